@@ -120,6 +120,28 @@ bool pairs_of_halves(const Scheme& s, int64_t* inner, int64_t* outer) {
   return true;
 }
 
+// Launch group g's products one by one (E2M1 or E2M3 planes, numbered from the first plane of
+// the group's format), folded at least every k_seg indices.  With the weights in the scales, the
+// products take the weights as coefficients instead; each then accumulates on its own, so its
+// bound is that of its planes, not of the shared weighted sum.
+FlatProducts flat_products(const Scheme& s, int g, int first_a, int first_b, int64_t k_seg, bool own_seg) {
+  FlatProducts f{};
+  if (s.lfmt[g] == kFmtE4M3) return f;
+  for (int k = 0; k < s.r; ++k) {
+    if (s.lgroup[k] != g) continue;
+    f.pa[f.r] = s.pa[k] - first_a;
+    f.pb[f.r] = s.pb[k] - first_b;
+    f.ell[f.r] = (int32_t)(s.ell[k] / s.louter[g]);
+    ++f.r;
+  }
+  f.k_seg = k_seg;
+  if (s.scale_weights) {
+    const int64_t bound = ((int64_t(1) << 23) - 1) / ((int64_t)s.c_a * s.c_b) / kKPad * kKPad;
+    f.k_seg = own_seg ? bound : std::min(k_seg, bound);
+  }
+  return f;
+}
+
 // The launches of one exact or mod-m GEMM on stored planes, in order (every launch after
 // the first adds into C); nothing is enqueued.
 awe_status plan_gemm(const Scheme& s, int64_t M, int64_t N, int64_t K, const void* pa, const void* pb,
@@ -241,6 +263,7 @@ awe_status plan_gemm(const Scheme& s, int64_t M, int64_t N, int64_t K, const voi
         ++L.r;
       }
       L.outer = s.louter[g];
+      L.flat = flat_products(s, g, first_a, first_b, L.k_seg, own_seg);
       L.k_begin = k0;
       L.k_end = std::min(kp, k0 + step);
       L.accumulate = k0 > 0 || g > 0;

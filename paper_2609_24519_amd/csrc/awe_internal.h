@@ -2,6 +2,8 @@
 #pragma once
 #include <array>
 #include <cstdint>
+#include <mutex>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -147,6 +149,15 @@ struct EncodeLaunch {
 };
 awe_status launch_encode(const EncodeLaunch& e, hipStream_t stream);
 
+// A launch's products one by one, each plane pair with its own coefficient and no accumulator
+// sharing between products (r = 0: the launch has no such form), and their fold segment.
+struct FlatProducts {
+  int r;
+  int32_t pa[kMaxProducts], pb[kMaxProducts];
+  int32_t ell[kMaxProducts];
+  int64_t k_seg;
+};
+
 struct GemmLaunch {
   const uint8_t* planes_a;
   const uint8_t* planes_b;
@@ -178,6 +189,7 @@ struct GemmLaunch {
   bool accumulate;
   int log2D;
   int32_t modulus;
+  FlatProducts flat;
 };
 awe_status launch_gemm(const GemmLaunch& g, hipStream_t stream);
 
@@ -187,6 +199,18 @@ awe_status launch_gemm(const GemmLaunch& g, hipStream_t stream);
 constexpr int kGroupProducts = 4;
 bool gemm_group_ok(const GemmLaunch* L, int n);
 awe_status launch_gemm_group(const GemmLaunch* L, int n, hipStream_t stream);
+
+// ---- outputs of few tiles (awe_small.hip) ----
+// A variant of the kernel whose waves split the reduction (0: none), and workgroups per tile.
+struct Slice {
+  int variant, split;
+};
+// The variant that suits a launch, if it beats the tile configurations' `tile_us` on `cus` CUs.
+Slice choose_slice(const GemmLaunch& L, int cus, double tile_us);
+awe_status launch_slice(const GemmLaunch& L, Slice s, hipStream_t stream);
+
+// Raises a kernel's dynamic LDS limit to `bytes` once per device (`done`, guarded by `mu`).
+awe_status set_lds_limit(const void* fn, int bytes, std::mutex& mu, std::set<int>& done);
 
 // ---- residue number system (awe_rns.hip) ----
 constexpr int kMaxModuli = AWE_MAX_MODULI;

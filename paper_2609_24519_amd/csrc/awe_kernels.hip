@@ -11,6 +11,7 @@
 #include <type_traits>
 
 #include "awe_internal.h"
+#include "gemm_device.h"
 #include "gemm_layout.h"
 #include "plane_pack.h"
 
@@ -26,12 +27,6 @@ __device__ uint32_t g_wide_lut[2][kWideValues];
 static __device__ __align__(256) uint8_t scratch[kNoallocBytes];
 
 namespace {
-
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 struct LutArg {
   uint32_t v[256];
@@ -283,9 +278,6 @@ __global__ __launch_bounds__(256) void encode16_kernel(const int16_t* __restrict
 // (8 bytes of registers), so the register file bounds the tile; the operand
 // bytes each CU must pull through its L1 per MFMA fall as the tile grows.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kScale2 = 0x80808080u;  // E8M0 2^1 in every byte
-
-
 struct GemmArgs {
   const uint8_t* pa;
   const uint8_t* pb;
@@ -335,22 +327,6 @@ __device__ __forceinline__ void cursor_next(Cursor& c, const GemmArgs& g, int t_
   c.ce = end_all ? c.ce : nce;
 }
 
-// One 16-byte-per-lane global -> LDS copy: the wave's 64 lanes fill the 1 KiB
-// at LDS byte address `lds` (wave-uniform, in M0).  The brick's base address
-// is wave-uniform (SGPRs); every lane adds its own 16-byte offset `voff`.
-// Issued as inline assembly so that the compiler does not serialise the
-// copies; completion is awaited explicitly with vmcnt.
-__device__ __forceinline__ void dma_brick(const uint8_t* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
-               : "memory");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // Wait until at most `stages` younger stages of this wave's copies are in flight.
 template <class C, int STAGES>
 __device__ __forceinline__ void wait_stages(int wave) {
@@ -359,13 +335,6 @@ __device__ __forceinline__ void wait_stages(int wave) {
   else
     wait_vmcnt<(C::A_PW + C::B_LO) * C::COPIES * STAGES>();
 }
-
-// Workgroup barrier that is also a compiler memory barrier: no LDS access may
-// move across it.  The caller has already waited for its own copies (vmcnt)
-// and LDS reads (lgkmcnt) as the protocol needs.
-__device__ __forceinline__ void block_barrier() { asm volatile("s_barrier" ::: "memory"); }
-
-__device__ __forceinline__ void wait_lgkm0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // The copies of one stage (units as copy_unit assigns them; addresses from gemm_layout.h).
 template <class C>
@@ -434,35 +403,6 @@ __device__ __forceinline__ void load_one(const GemmArgs& g, const Cursor& c, uin
   }
 }
 
-__device__ __forceinline__ v8i frag(const uint8_t* p) {
-  const int4 x = *reinterpret_cast<const int4*>(p);
-  v8i v = {x.x, x.y, x.z, x.w, 0, 0, 0, 0};
-  return v;
-}
-
-// A lane's fragment of k-step i of a unit (the spans of frag_spans): E2M1 16 bytes, E4M3 32
-// bytes, E2M3 24 bytes (the MFMA reads 6 of the 8 operand registers for E2M3, so the last two
-// are left undefined instead of zeroed, which would cost two registers per fragment).
-template <int FMT>
-__device__ __forceinline__ v8i frag_fmt(const uint8_t* unit, int i, int lane) {
-  constexpr Spans z = frag_spans<FMT>(0, 0);
-  const Spans sp = frag_spans<FMT>(i, lane);
-  if constexpr (FMT == 0) {
-    return frag(unit + sp.off[0]);
-  } else if constexpr (FMT == 1) {
-    const int4 x = *reinterpret_cast<const int4*>(unit + sp.off[0]);
-    const int4 y = *reinterpret_cast<const int4*>(unit + sp.off[0] + 16);
-    v8i v = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-    return v;
-  } else {
-    static_assert(z.n == 2 && z.len[0] == 16 && z.len[1] == 8, "E2M3 spans");
-    const v4i x = *reinterpret_cast<const v4i*>(unit + sp.off[0]);
-    const v2i y = *reinterpret_cast<const v2i*>(unit + sp.off[1]);
-    const v4i y4 = __builtin_shufflevector(y, y, 0, 1, -1, -1);
-    return __builtin_shufflevector(x, y4, 0, 1, 2, 3, 4, 5, -1, -1);
-  }
-}
-
 // The wave's operand fragments for one k-step (64 reduction indices) of a stage.
 template <class C>
 struct Frags {
@@ -496,24 +436,6 @@ __device__ __forceinline__ void read_frags(Frags<C>& f, const uint8_t* stage, in
 #pragma unroll
     for (int j = 0; j < C::BNW; ++j)
       f.b[pl * C::BNW + j] = frag_fmt<C::FMT>(stage + frag_unit<C>(false, pl, wn * C::BNW + j, ks), i, lane);
-}
-
-__device__ __forceinline__ void mfma_block(v16f& acc, const v8i& a, const v8i& b) {
-  acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 4, 4, 0, kScale2, 0, kScale2);
-}
-
-// E4M3 x E4M3 (format selects 0): the stored E4M3 values are the integers
-// themselves, so both block scales are 2^0 (byte 127).
-constexpr uint32_t kScale1 = 0x7f7f7f7fu;
-__device__ __forceinline__ void mfma_block8(v16f& acc, const v8i& a, const v8i& b) {
-  acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 0, 0, 0, kScale1, 0, kScale1);
-}
-
-// E2M3 x E2M3 (format selects 2): a stored integer n is the E2M3 value n / 8, so
-// both block scales are 2^3 (byte 130) and each product of codes is n_a n_b.
-constexpr uint32_t kScale8 = 0x82828282u;
-__device__ __forceinline__ void mfma_block6(v16f& acc, const v8i& a, const v8i& b) {
-  acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 2, 2, 0, kScale8, 0, kScale8);
 }
 
 #ifndef AWE_GEMM_GROUP_M
@@ -624,15 +546,6 @@ __global__ __launch_bounds__(256) void zero_tiles_kernel(GemmArgs g, int bm, int
       else
         reinterpret_cast<int32_t*>(g.C)[row + c] = 0;
     }
-  }
-}
-
-// f(integral_constant<int, Q>) for Q = I .. N - 1, unrolled at compile time.
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
   }
 }
 
@@ -1241,6 +1154,31 @@ double rounds(int64_t tiles, int cus) {
   return (double)full + (full > 0 && S >= 2 ? 1.0 / S : 1.0);
 }
 
+// Parts into which every tile's reduction is split when the tiles alone leave CUs idle (fewer
+// tiles than CUs), and the estimated time with it (units of 10 ns).  `work` and `fixed`: the time of
+// a tile's MFMAs and of its prologue and epilogue; `stages`: stages of the whole reduction.  S
+// parts per tile take work / S, but C is zeroed first (a small launch) and receives S atomic
+// additions per output: the eight L2s complete 270 of these per ns together (one per clock and
+// channel, for int32 and int64 alike: 2048^2 outputs cost 16 us per part), so a split pays for
+// long reductions and few outputs.  It stays within one round, with at least two stages a part.
+// AWE_GEMM_SPLIT forces the number of parts (it changes no result).
+struct Split {
+  int parts;
+  double time;
+};
+Split best_split(int64_t tiles, int cus, int stages, double work, double fixed, double outputs, bool allowed) {
+  Split best{1, rounds(tiles, cus) * (work + fixed)};
+  if (!allowed) return best;
+  const char* e = getenv("AWE_GEMM_SPLIT");
+  const int forced = e ? atoi(e) : 0;
+  if (forced > 0) return forced <= stages ? Split{forced, best.time} : best;
+  for (int s = 2; s <= 16 && tiles * s <= cus && stages >= 2 * s; ++s) {
+    const double t = work / s + fixed + 400.0 + s * outputs / 2700.0;
+    if (t < best.time) best = Split{s, t};
+  }
+  return best;
+}
+
 // Whether n names one of the E2M1 tile configurations (AWE_GEMM_CFG): 1: 256x128 with 8
 // waves, 2: 256x192 with 8 waves, 4: as 1 with 4 k-steps per stage, 5: as 4 with fragments
 // read three k-steps ahead, 6: 256x192 with 4 k-steps per stage in 2 stages, 7: 256x192 with 2
@@ -1253,27 +1191,33 @@ double rounds(int64_t tiles, int cus) {
 // during the rest of it.
 bool e2m1_cfg(int n) { return n == 1 || n == 2 || (n >= 4 && n <= 17 && n != 11 && n != 14); }
 
-// Tile configuration for a problem: AWE_GEMM_CFG if it names one, else the configuration whose
-// rounds of workgroups finish first: 5, 6 (a round about 1.48 times as long as a round of 5;
-// only when clearly sooner) or 17.  A round takes about 2.05 k + 1090 time units (10 ns) for 5
-// and 3.76 k + 1800 for 17, k = r K / 6 reduction indices at r products: a fit of the kernel
-// times measured on one MI355X for 8192^2 outputs at K = 2048 .. 8192 (r = 6); it also orders
-// 4096^2 outputs at K = 4096 .. 16384 with 1 to 6 products, 6144^3 and 2048^2 x 8192 as
-// measured.  The larger tile moves fewer bytes per MAC but fills the chip only with enough
-// tiles: at 2048^2 x 8192 its 64 tiles leave most CUs idle and 5 wins.
-int choose_cfg(int64_t M, int64_t N, int r, int64_t K) {
+// Tile configuration for a problem and its estimated time (10 ns): AWE_GEMM_CFG if it names one,
+// else the configuration whose rounds of workgroups finish first, each with its best split of
+// the reduction: 5, 6 (a round about 1.48 times as long as a round of 5; only when clearly sooner)
+// or 17.  A round takes about 2.05 k + 1090 time units for 5 and 3.76 k + 1800 for 17,
+// k = r K / 6 reduction indices at r products: a fit of the kernel times measured on one MI355X for
+// 8192^2 outputs at K = 2048 .. 8192 (r = 6); it also orders 4096^2 outputs at K = 4096 .. 16384
+// with 1 to 6 products and 6144^3 as measured.
+struct Choice {
+  int cfg;
+  double time;
+};
+Choice choose_cfg(const GemmLaunch& L) {
   const char* e = getenv("AWE_GEMM_CFG");
   const int forced = e ? atoi(e) : -1;
-  if (e2m1_cfg(forced)) return forced;
+  if (e2m1_cfg(forced)) return Choice{forced, 0.0};
   const int cus = compute_units();
-  const int64_t tm = (M + 255) / 256;
-  const double k = (double)r * (double)K / 6.0;
-  const double r128 = 2.05 * k + 1090.0, r256 = 3.76 * k + 1800.0;
-  const double t128 = rounds(tm * ((N + 127) / 128), cus) * r128;
-  const double t192 = rounds(tm * ((N + 191) / 192), cus) * 1.48 * r128;
-  const double t256 = rounds(tm * ((N + 255) / 256), cus) * r256;
-  if (t256 < t128 && t256 < t192) return 17;
-  return t192 < 0.97 * t128 ? 6 : 5;
+  const int64_t tm = (L.M + 255) / 256, len = L.k_end - L.k_begin;
+  const double k = (double)L.r * (double)len / 6.0, outs = (double)L.M * (double)L.N;
+  const bool split = !L.modulus;
+  const double t128 =
+      best_split(tm * ((L.N + 127) / 128), cus, (int)(len / 256), 2.05 * k, 1090.0, outs, split).time;
+  const double t192 = best_split(tm * ((L.N + 191) / 192), cus, (int)(len / 256), 1.48 * 2.05 * k, 1.48 * 1090.0,
+                                 outs, split).time;
+  const double t256 =
+      best_split(tm * ((L.N + 255) / 256), cus, (int)(len / 128), 3.76 * k, 1800.0, outs, split).time;
+  if (t256 < t128 && t256 < t192) return Choice{17, t256};
+  return t192 < 0.97 * t128 ? Choice{6, t192} : Choice{5, t128};
 }
 
 // Tile configuration of a grouped launch of n jobs of one shape: AWE_GEMM_CFG if set, else 5
@@ -1337,21 +1281,18 @@ void fill_args(const GemmLaunch& L, GemmArgs& g) {
   g.outer = L.outer;
 }
 
-// Raises a kernel's dynamic LDS limit to `bytes` once per device (the GEMM's ring exceeds
-// the default).
-awe_status set_lds_limit(const void* fn, int bytes, std::mutex& mu, std::set<int>& done) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  std::lock_guard<std::mutex> lk(mu);
-  if (e == hipSuccess && !done.count(dev)) {
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess) done.insert(dev);
-  }
-  if (e != hipSuccess) {
-    set_error(std::string("gemm LDS attribute: ") + hipGetErrorString(e));
-    return AWE_ERR_HIP;
-  }
-  return AWE_OK;
+// The split of a launch on one tile configuration, with its estimated time: 0.7 time units (10 ns)
+// per 32x32x64 MFMA of a tile (twice that for E4M3's) and 1400 for prologue and epilogue, or 0.5 and
+// 800 where a stage's planes serve several products, near the measured times of every
+// configuration.
+template <class C>
+Split tile_split(const GemmLaunch& L, int cus) {
+  const int64_t tiles = ((L.M + C::BM - 1) / C::BM) * ((L.N + C::BN - 1) / C::BN), len = L.k_end - L.k_begin;
+  const double mfmas = (double)L.r * (C::AP ? C::NPA * C::NPB : C::NPL * C::NPL) * (C::BM / 32) * (C::BN / 32) *
+                       (double)(len / kBrickK);
+  return best_split(tiles, cus, (int)(len / C::KT), (C::FMT == 1 ? 1.4 : C::AP ? 0.5 : 0.7) * mfmas,
+                    C::AP ? 800.0 : 1400.0,
+                    (double)L.M * (double)L.N, !L.modulus);
 }
 
 template <class C>
@@ -1364,16 +1305,22 @@ awe_status launch_tile(GemmArgs& g, const GemmLaunch& L, hipStream_t stream) {
   g.tiles_n = (int32_t)tiles_n;
   const int64_t tiles = tiles_m * tiles_n;
   if (tiles > 0x3fffffffLL) return AWE_ERR_UNSUPPORTED;
-  // A ragged last round of workgroups (rem tiles on cus CUs) is split along the
-  // reduction: each of its tiles is computed by S = min(cus / rem, 4) workgroups
-  // over consecutive parts of the range, so that round takes about 1/S of a
-  // tile's time.  Residues need the whole sum before their reduction mod m and
-  // are never split.
+  // The reduction is split over several workgroups (which add their exact partials into C) in
+  // two cases.  Fewer tiles than CUs: every tile, into the parts best_split picks.  A ragged last
+  // round (rem tiles on cus CUs): its tiles, into S = min(cus / rem, 4) parts, so that round takes
+  // about 1/S of a tile's time.  Residues need the whole sum before their reduction mod m and are
+  // never split.
   const int cus = compute_units();
   const int stages = g.t_end - g.t_begin;
   g.n_full = (int32_t)tiles;
   g.split = 1;
-  if (!L.modulus && tiles > cus && tiles % cus != 0) {
+  if (!L.modulus && tiles < cus) {
+    const Split s = tile_split<C>(L, cus);
+    if (s.parts > 1) {
+      g.n_full = 0;
+      g.split = s.parts;
+    }
+  } else if (!L.modulus && tiles > cus && tiles % cus != 0) {
     const int64_t rem = tiles % cus;
     const int S = (int)std::min<int64_t>(cus / rem, 4);
     if (S >= 2 && stages >= 2 * S) {
@@ -1461,6 +1408,23 @@ awe_status launch_group_tile(const GemmLaunch* L, const int* order, int n, hipSt
 }
 
 }  // namespace
+
+// Raises a kernel's dynamic LDS limit to `bytes` once per device (the GEMM's ring exceeds
+// the default).
+awe_status set_lds_limit(const void* fn, int bytes, std::mutex& mu, std::set<int>& done) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  std::lock_guard<std::mutex> lk(mu);
+  if (e == hipSuccess && !done.count(dev)) {
+    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.insert(dev);
+  }
+  if (e != hipSuccess) {
+    set_error(std::string("gemm LDS attribute: ") + hipGetErrorString(e));
+    return AWE_ERR_HIP;
+  }
+  return AWE_OK;
+}
 
 // Uploads a wide encoding's code table into g_wide_lut on the current device,
 // once per device and side (the table never changes afterwards: one wide
@@ -1581,6 +1545,22 @@ awe_status launch_gemm(const GemmLaunch& L, hipStream_t stream) {
     }
     return AWE_OK;
   }
+  // Outputs of few tiles: the kernel whose waves split the reduction, where it is sooner done than
+  // the tile configuration below (only if that one is not asked for).
+  const int cus = compute_units();
+  double tile_time = 0.0;
+  if (L.flat.r > 0) {
+    if (L.allpairs_a)
+      tile_time = tile_split<Cfg8w32x64ap33>(L, cus).time;
+    else if (L.shared)
+      tile_time = tile_split<Cfg8w64x64sh>(L, cus).time;
+    else if (L.fmt == kFmtE2M3)
+      tile_time = tile_split<Cfg8w64x96p0lfe2m3>(L, cus).time;
+    else
+      tile_time = choose_cfg(L).time;
+  }
+  const Slice slice = choose_slice(L, cus, tile_time / 100.0);
+  if (slice.variant) return launch_slice(L, slice, stream);
   GemmArgs g{};
   fill_args(L, g);
   if (L.fmt == kFmtE4M3) return launch_tile<Cfg8w64x64e4m3>(g, L, stream);
@@ -1608,7 +1588,7 @@ awe_status launch_gemm(const GemmLaunch& L, hipStream_t stream) {
       default: return launch_tile<Cfg8w64x64e2m3>(g, L, stream);
     }
   }
-  switch (choose_cfg(L.M, L.N, L.r, L.k_end - L.k_begin)) {
+  switch (choose_cfg(L).cfg) {
     case 2: return launch_tile<Cfg8w64x96>(g, L, stream);
     case 4: return launch_tile<Cfg8w64x64k4>(g, L, stream);
     case 5: return launch_tile<Cfg8w64x64k4p3>(g, L, stream);

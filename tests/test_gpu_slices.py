@@ -1,0 +1,102 @@
+"""The GEMM for outputs of few tiles (its waves split the reduction) and the reduction splits of
+the tile configurations, bit-exact against the oracle: every variant at the edges of its tiles, with
+reductions shorter than the shares, forced fold segments, several workgroups per tile, residues
+and reductions over several launches."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import gemm as oracle_gemm
+from paper_2609_24519_amd import awe, inputs
+from tests.gpu_helpers import device, to_dev
+
+pytestmark = pytest.mark.gpu
+
+TILES = {1: (128, 128), 2: (64, 128), 3: (64, 64), 4: (32, 32), 5: (32, 64), 6: (64, 32)}
+ENCS = [awe.ENC_AWE6, awe.ENC_AWE4, awe.ENC_B13, awe.ENC_TERNARY, awe.ENC_FP6K3, awe.ENC_FP6P4]
+
+
+def _product(enc, A, B, out, kseg=0, ldc_pad=0):
+    M, K = A.shape
+    N = B.shape[1]
+    dA, dB = to_dev(A), to_dev(B)
+    pa = torch.empty(awe.plane_bytes(enc, 0, awe.SIDE_A, M, K), dtype=torch.uint8, device=device())
+    pb = torch.empty(awe.plane_bytes(enc, 0, awe.SIDE_B, N, K), dtype=torch.uint8, device=device())
+    awe.encode(enc, 0, awe.SIDE_A, dA, M, K, K, pa)
+    awe.encode(enc, 0, awe.SIDE_B, dB, N, K, N, pb)
+    C = torch.full((M, N + ldc_pad), -7, dtype=out, device=device())
+    awe.gemm_planes(enc, 0, M, N, K, pa, pb, C, N + ldc_pad, awe.I64 if out == torch.int64 else awe.I32, kseg)
+    torch.cuda.synchronize()
+    C = C.cpu().numpy()
+    assert (C[:, N:] == -7).all()
+    return C[:, :N].astype(np.int64)
+
+
+def _operands(enc, M, N, K, seed):
+    info = awe.get_encoding_info(enc)
+    return inputs.int8_pair(M, N, K, seed, info["range_a"], info["range_b"])
+
+
+@pytest.mark.parametrize("variant", sorted(TILES))
+@pytest.mark.parametrize("enc", ENCS)
+def test_every_variant(monkeypatch, variant, enc):
+    monkeypatch.setenv("AWE_GEMM_SLICE", str(variant))
+    bm, bn = TILES[variant]
+    # one ragged tile with a reduction shorter than the shares; more than a tile either way, an odd
+    # ldc and several items per share; whole tiles
+    for M, N, K, pad, out in [(bm - 1, 1, 1, 0, torch.int32), (bm + 1, 2 * bn + 3, 1300, 2, torch.int32),
+                              (2 * bm, bn, 515, 0, torch.int64)]:
+        A, B = _operands(enc, M, N, K, variant * 100 + M)
+        assert np.array_equal(_product(enc, A, B, out, ldc_pad=pad), oracle_gemm.gemm_i64(A, B)), (M, N, K)
+
+
+@pytest.mark.parametrize("variant", [1, 3, 4])
+@pytest.mark.parametrize("enc", [awe.ENC_AWE6, awe.ENC_FP6P4])
+@pytest.mark.parametrize("split", ["1", "3"])
+def test_fold_segments_and_split_tiles(monkeypatch, variant, enc, split):
+    monkeypatch.setenv("AWE_GEMM_SLICE", str(variant))
+    monkeypatch.setenv("AWE_GEMM_SLICE_SPLIT", split)
+    A, B = _operands(enc, 70, 133, 2600, 5)
+    ref = oracle_gemm.gemm_i64(A, B)
+    for kseg in (awe.K_PAD, 2 * awe.K_PAD, 0):
+        for out in (torch.int32, torch.int64):
+            assert np.array_equal(_product(enc, A, B, out, kseg, 1), ref), (kseg, out)
+
+
+@pytest.mark.parametrize("variant", sorted(TILES))
+@pytest.mark.parametrize("m", [7, 89, 157])
+def test_residues(monkeypatch, variant, m):
+    monkeypatch.setenv("AWE_GEMM_SLICE", str(variant))
+    for M, N, K in [(1, 1, 1), (130, 70, 1111)]:
+        A, B = inputs.residue_pair(M, N, K, m)
+        C = awe.matmul_mod(m, to_dev(A), to_dev(B)).cpu().numpy()
+        assert np.array_equal(C, oracle_gemm.gemm_mod(m, A, B)), (M, N, K)
+
+
+def test_several_launches_add_up(monkeypatch):
+    # int8 launches cover 130,816 indices; the second adds into C, with and without split tiles
+    A, B = inputs.int8_pair(33, 40, 150000, 9)
+    ref = oracle_gemm.gemm_i64(A, B)
+    for variant, split in (("4", "1"), ("3", "4"), ("1", "2")):
+        monkeypatch.setenv("AWE_GEMM_SLICE", variant)
+        monkeypatch.setenv("AWE_GEMM_SLICE_SPLIT", split)
+        assert np.array_equal(_product(awe.ENC_AWE6, A, B, torch.int64), ref), (variant, split)
+
+
+@pytest.mark.parametrize("parts", ["2", "3", "5"])
+@pytest.mark.parametrize("enc,out", [(awe.ENC_AWE6, torch.int32), (awe.ENC_AWE4, torch.int64), (awe.ENC_B13, torch.int32),
+                                     (awe.ENC_FP6K3, torch.int32), (awe.ENC_FP6P4, torch.int64),
+                                     (awe.ENC_FP8FP4, torch.int32)])
+def test_split_of_every_tile(monkeypatch, parts, enc, out):
+    # fewer tiles than CUs: each tile's reduction in `parts` parts, the last one shorter
+    monkeypatch.setenv("AWE_GEMM_SPLIT", parts)
+    A, B = _operands(enc, 300, 270, 2900, int(parts))
+    assert np.array_equal(_product(enc, A, B, out, ldc_pad=1), oracle_gemm.gemm_i64(A, B))
+
+
+def test_chosen_route_on_mixed_shapes():
+    # the library's own choice, over shapes that take different routes
+    for enc, M, N, K in [(awe.ENC_AWE6, 16, 2000, 1500), (awe.ENC_B13, 700, 130, 900), (awe.ENC_AWE6, 64, 64, 20000),
+                         (awe.ENC_FP6P4, 130, 900, 700), (awe.ENC_TERNARY, 1, 5000, 300), (awe.ENC_AWE4, 2100, 1900, 300)]:
+        A, B = _operands(enc, M, N, K, M)
+        assert np.array_equal(_product(enc, A, B, torch.int32), oracle_gemm.gemm_i64(A, B)), (enc, M, N, K)
