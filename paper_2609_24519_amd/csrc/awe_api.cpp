@@ -282,15 +282,17 @@ awe_status gemm_planes_impl(const Scheme& s, int64_t M, int64_t N, int64_t K, co
   return st;
 }
 
-awe_status encode_impl(const Scheme& s, awe_side side, const void* x, int64_t rows, int64_t K,
-                       int64_t ld, void* planes, int32_t* flag, hipStream_t stream) {
+// Argument checks and the launch description of one side (launch->rows == 0: no bricks).
+awe_status plan_encode(const Scheme& s, awe_side side, const void* x, int64_t rows, int64_t K, int64_t ld,
+                       void* planes, int32_t* flag, EncodeLaunch* launch) {
+  EncodeLaunch& e = *launch;
+  e = EncodeLaunch{};
   if (side != AWE_SIDE_A && side != AWE_SIDE_B) return fail(AWE_ERR_INVALID_VALUE, "bad side");
   if (rows < 0 || K < 0) return fail(AWE_ERR_INVALID_VALUE, "negative size");
   if (rows == 0 || K == 0) return AWE_OK;  // no bricks
   if (x == nullptr || planes == nullptr) return fail(AWE_ERR_INVALID_VALUE, "NULL pointer");
   const bool sideA = side == AWE_SIDE_A;
   if (sideA ? ld < K : ld < rows) return fail(AWE_ERR_INVALID_VALUE, "leading dimension too small");
-  EncodeLaunch e{};
   e.x = x;
   e.rows = rows;
   e.K = K;
@@ -309,7 +311,14 @@ awe_status encode_impl(const Scheme& s, awe_side side, const void* x, int64_t ro
   e.nvalues = s.table_size(sideA);
   e.side = sideA ? 0 : 1;
   e.table_key = &s;
-  return launch_encode(e, stream);
+  return AWE_OK;
+}
+
+awe_status encode_impl(const Scheme& s, awe_side side, const void* x, int64_t rows, int64_t K,
+                       int64_t ld, void* planes, int32_t* flag, hipStream_t stream) {
+  EncodeLaunch e;
+  const awe_status st = plan_encode(s, side, x, rows, K, ld, planes, flag, &e);
+  return st != AWE_OK || e.rows == 0 ? st : launch_encode(e, stream);
 }
 
 awe_status exact_impl(const Scheme& s, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
@@ -332,9 +341,13 @@ awe_status exact_impl(const Scheme& s, int64_t M, int64_t N, int64_t K, const vo
   uint8_t* pb = pa + ba;
   awe_status st = AWE_OK;
   if (K > 0) {
-    st = encode_impl(s, AWE_SIDE_A, A, M, K, lda, pa, flag, stream);
+    EncodeLaunch ea, eb;
+    st = plan_encode(s, AWE_SIDE_A, A, M, K, lda, pa, flag, &ea);
     if (st != AWE_OK) return st;
-    st = encode_impl(s, AWE_SIDE_B, B, N, K, ldb, pb, flag, stream);
+    st = plan_encode(s, AWE_SIDE_B, B, N, K, ldb, pb, flag, &eb);
+    if (st != AWE_OK) return st;
+    ea.other = &eb;  // one launch for both
+    st = launch_encode(ea, stream);
     if (st != AWE_OK) return st;
   }
   return gemm_planes_impl(s, M, N, K, pa, pb, C, ldc, c_type, 0, stream);

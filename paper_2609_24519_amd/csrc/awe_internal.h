@@ -146,6 +146,7 @@ struct EncodeLaunch {
   int32_t xmin, nvalues;
   int side;             // which of the two device-resident wide tables to use
   const void* table_key;  // identity of the wide table (its Scheme)
+  const EncodeLaunch* other;  // the other side of the same product, encoded by the same launch (nullable)
 };
 awe_status launch_encode(const EncodeLaunch& e, hipStream_t stream);
 

@@ -39,23 +39,51 @@ struct LutArg {
 // plane values (combinations of limbs included) come from one 256-entry table
 // of packed E2M1 codes, so forming a combination plane costs nothing here.
 // ---------------------------------------------------------------------------
-// At least four waves per SIMD (at most 128 registers): the encoder is HBM-bound and needs that
-// many loads in flight (the B side took 15 % longer at three).
+struct EncodeArgs {
+  const uint8_t* x;
+  int64_t rows, K, ld, KS, R32, nbricks;
+  int nplanes, nplanes8;
+  bool fp6;
+  uint8_t* planes;
+  int64_t plane_stride;
+  int32_t* flag;
+};
+
+// 16 and 8 bytes from any address (the memory system takes unaligned vector loads; rows of an odd
+// length were read byte by byte before: 14 us a side at 1001 x 2049 and 2049 x 1537).
+struct __attribute__((packed)) Any16 {
+  uint32_t w[4];
+};
+struct __attribute__((packed)) Any8 {
+  uint32_t w[2];
+};
+
+// The 4 x 4 byte transpose of v (v[i] holds bytes 0 .. 3 of row i): out[j] holds byte j of rows 0 .. 3.
+__device__ __forceinline__ void transpose4x4(const uint32_t (&v)[4], uint32_t (&out)[4]) {
+  const uint32_t t0 = __builtin_amdgcn_perm(v[1], v[0], 0x05010400u);
+  const uint32_t t1 = __builtin_amdgcn_perm(v[1], v[0], 0x07030602u);
+  const uint32_t t2 = __builtin_amdgcn_perm(v[3], v[2], 0x05010400u);
+  const uint32_t t3 = __builtin_amdgcn_perm(v[3], v[2], 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
+  out[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
+  out[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
+  out[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
+}
+
+// B side: a wave's 64 x 32 input block lies column-major in LDS, kTileCol bytes per column (64 rows +
+// 16 bytes of padding, so that the 16-byte column reads hit distinct banks).
+constexpr int kTileCol = 80;
+
+// The bricks of one side that workgroup `block` of `blocks` produces.
 template <bool kTransposed>
-__global__ __launch_bounds__(256, 4) void encode_kernel(const uint8_t* __restrict__ x, int64_t rows,
-                                                     int64_t K, int64_t ld, int64_t KS,
-                                                     int64_t R32, int64_t nbricks, int nplanes,
-                                                     int nplanes8, bool fp6,
-                                                     uint8_t* __restrict__ planes,
-                                                     int64_t plane_stride, int32_t* flag,
-                                                     LutArg lut) {
-  __shared__ uint32_t slut[256];
-  // B side: per-wave 64 x 32 input block stored column-major, kTileCol bytes per column (64
-  // rows + 16 bytes of padding, so that the 16-byte column reads below hit distinct banks)
-  constexpr int kTileCol = 80;
-  __shared__ __attribute__((aligned(16))) uint8_t tblk[kTransposed ? 4 : 1][kTransposed ? 32 * kTileCol : 1];
-  slut[threadIdx.x] = lut.v[threadIdx.x];
-  __syncthreads();
+__device__ __forceinline__ void encode_side(const EncodeArgs& a, const uint32_t* slut, uint8_t* tblk, unsigned block,
+                                            unsigned blocks) {
+  const uint8_t* __restrict__ x = a.x;
+  uint8_t* __restrict__ planes = a.planes;
+  const int64_t rows = a.rows, K = a.K, ld = a.ld, KS = a.KS, R32 = a.R32, nbricks = a.nbricks;
+  const int64_t plane_stride = a.plane_stride;
+  const int nplanes = a.nplanes, nplanes8 = a.nplanes8;
+  int32_t* flag = a.flag;
   const int lane = threadIdx.x & 63;
   // Each wave takes one brick, or several when the grid is capped.  A side: the four waves of
   // a workgroup take four consecutive k-steps of one row block (32 rows x 256 bytes of A).
@@ -66,8 +94,7 @@ __global__ __launch_bounds__(256, 4) void encode_kernel(const uint8_t* __restric
   // groups of one k-step, so that the workgroups in flight read whole rows of B (measured 3-7 %
   // faster from HBM than consecutive k-steps of one column group).  Here nbricks counts
   // ceil(R32 / 4) * 4 row blocks on the B side, and the waves past R32 have no brick.
-  for (int64_t brick = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); brick < nbricks;
-       brick += (int64_t)gridDim.x * 4) {
+  for (int64_t brick = (int64_t)block * 4 + (threadIdx.x >> 6); brick < nbricks; brick += (int64_t)blocks * 4) {
   int64_t rb, ks;
   if (kTransposed) {
     const int64_t q = brick >> 2, groups = (R32 + 3) / 4;
@@ -85,51 +112,60 @@ __global__ __launch_bounds__(256, 4) void encode_kernel(const uint8_t* __restric
   uint32_t e[32];
   if (!kTransposed) {
     const uint8_t* src = x + row * ld + k0;
-    if (row_ok && k0 + 32 <= K && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-      const uint4 lo = *reinterpret_cast<const uint4*>(src);
-      const uint4 hi = *reinterpret_cast<const uint4*>(src + 16);
-      const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    if (row_ok && k0 + 32 <= K) {
+      const Any16 lo = *reinterpret_cast<const Any16*>(src), hi = *reinterpret_cast<const Any16*>(src + 16);
 #pragma unroll
-      for (int j = 0; j < 32; ++j) e[j] = slut[(w[j >> 2] >> (8 * (j & 3))) & 0xff];
+      for (int j = 0; j < 32; ++j) e[j] = slut[((j < 16 ? lo.w[j >> 2] : hi.w[(j - 16) >> 2]) >> (8 * (j & 3))) & 0xff];
     } else {
 #pragma unroll
-      for (int j = 0; j < 32; ++j) e[j] = (row_ok && k0 + j < K) ? slut[src[j]] : 0u;
+      for (int j = 0; j < 32; ++j) e[j] = 0u;
+      if (row_ok && k0 < K) {
+#pragma unroll
+        for (int j = 0; j < 32; ++j)
+          if (k0 + j < K) e[j] = slut[src[j]];
+      }
     }
   } else {
     // B side, K x N row-major: the brick needs the 64 x 32 block of B at rows
-    // (reduction indices) ks*64 .. +63 and columns rb*32 .. +31.  Load i of lane l takes
-    // the 16 bytes at columns 16 (l & 1) .. +15 of block row 32 i + l / 2 (so each load
-    // instruction covers 32 rows x 32 bytes) and writes them into those columns of this
-    // wave's column-major tile; lane 32 h + t then reads rows 32 h .. 32 h + 31 of column t
-    // as two 16-byte words.
-    uint8_t* tw = tblk[threadIdx.x >> 6];
+    // (reduction indices) ks*64 .. +63 and columns rb*32 .. +31.  Lane l takes columns
+    // 8 (l & 3) .. +7 of block rows 4 (l >> 2) .. +3, transposes them in registers and writes four
+    // rows of each column as one word of this wave's column-major tile; lane 32 h + t then reads
+    // rows 32 h .. 32 h + 31 of column t as two 16-byte words.
+    uint8_t* tw = tblk + (threadIdx.x >> 6) * (32 * kTileCol);
     const int64_t n0 = rb * kBrickRows;
-    const int half = lane & 1;
+    const int c0 = 8 * (lane & 3), r0 = 4 * (lane >> 2);
+    const int64_t kr = ks * kBrickK + r0;
+    const uint8_t* src = x + kr * ld + n0 + c0;
+    uint32_t v[2][4];
+    if (n0 + 32 <= rows && kr + 4 <= K) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int r = 32 * i + (lane >> 1);
-      const int64_t kr = ks * kBrickK + r;
-      const uint8_t* src = x + kr * ld + n0 + 16 * half;
-      uint32_t w[4];
-      if (kr < K && n0 + 32 <= rows && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-        const uint4 v = *reinterpret_cast<const uint4*>(src);
-        w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-      } else {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) w[d] = 0;
-        for (int c = 0; c < 16; ++c)
-          if (kr < K && n0 + 16 * half + c < rows) w[c >> 2] |= (uint32_t)src[c] << (8 * (c & 3));
+      for (int i = 0; i < 4; ++i) {
+        const Any8 t = *reinterpret_cast<const Any8*>(src + i * ld);
+        v[0][i] = t.w[0];
+        v[1][i] = t.w[1];
       }
+    } else {
 #pragma unroll
-      for (int c = 0; c < 16; ++c)
-        tw[(16 * half + c) * kTileCol + r] = (uint8_t)(w[c >> 2] >> (8 * (c & 3)));
+      for (int i = 0; i < 4; ++i) {
+        v[0][i] = v[1][i] = 0;
+        if (kr + i < K)
+          for (int c = 0; c < 8; ++c)
+            if (n0 + c0 + c < rows) v[c >> 2][i] |= (uint32_t)src[i * ld + c] << (8 * (c & 3));
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      uint32_t t[4];
+      transpose4x4(v[h], t);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) *reinterpret_cast<uint32_t*>(tw + (c0 + 4 * h + c) * kTileCol + r0) = t[c];
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS writes are done
     __builtin_amdgcn_wave_barrier();
     const uint8_t* col = tw + (lane & 31) * kTileCol + (lane >> 5) * 32;
-    const uint4 c0 = *reinterpret_cast<const uint4*>(col);
-    const uint4 c1 = *reinterpret_cast<const uint4*>(col + 16);
-    const uint32_t cw[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+    const uint4 q0 = *reinterpret_cast<const uint4*>(col);
+    const uint4 q1 = *reinterpret_cast<const uint4*>(col + 16);
+    const uint32_t cw[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
 #pragma unroll
     for (int j = 0; j < 32; ++j)
       e[j] = (row_ok && k0 + j < K) ? slut[(cw[j >> 2] >> (8 * (j & 3))) & 0xff] : 0u;
@@ -139,7 +175,7 @@ __global__ __launch_bounds__(256, 4) void encode_kernel(const uint8_t* __restric
   for (int j = 0; j < 32; ++j) bad |= e[j];
   if ((bad & kLutInvalid) && flag != nullptr) atomicOr(flag, 1);
 
-  if (fp6) {
+  if (a.fp6) {
     // E2M3 planes (1.5 plane strides each) in 3 KiB units of two k-steps: lane L's 32
     // six-bit codes form 6 dwords, the first 4 at i*1024 + 16 L and the last 2 at
     // 2048 + i*512 + 8 L of the unit (i = ks & 1).
@@ -194,65 +230,163 @@ __global__ __launch_bounds__(256, 4) void encode_kernel(const uint8_t* __restric
   }  // bricks
 }
 
+// At least four waves per SIMD (at most 128 registers): the encoder is HBM-bound and needs that
+// many loads in flight (the B side took 15 % longer at three).
+template <bool kTransposed>
+__global__ __launch_bounds__(256, 4) void encode_kernel(EncodeArgs a, LutArg lut) {
+  __shared__ uint32_t slut[256];
+  __shared__ __attribute__((aligned(16))) uint8_t tblk[kTransposed ? 4 * 32 * kTileCol : 16];
+  slut[threadIdx.x] = lut.v[threadIdx.x];
+  __syncthreads();
+  encode_side<kTransposed>(a, slut, tblk, blockIdx.x, gridDim.x);
+}
+
+// Both operands of one product in one launch: workgroups 0 .. blocks_b - 1 encode B, the rest A
+// (AWE6, one launch against one per side: 4.7 us against 8.1 at 256^3, 12.0 / 17.9 at 2048^3, where
+// neither side alone keeps the memory busy, 88 / 100 at 8192^3).
+__global__ __launch_bounds__(256, 4) void encode_pair_kernel(EncodeArgs a, EncodeArgs b, unsigned blocks_b, LutArg lut_a,
+                                                             LutArg lut_b) {
+  __shared__ uint32_t slut[256];
+  __shared__ __attribute__((aligned(16))) uint8_t tblk[4 * 32 * kTileCol];
+  const bool side_b = blockIdx.x < blocks_b;
+  slut[threadIdx.x] = side_b ? lut_b.v[threadIdx.x] : lut_a.v[threadIdx.x];
+  __syncthreads();
+  if (side_b)
+    encode_side<true>(b, slut, tblk, blockIdx.x, blocks_b);
+  else
+    encode_side<false>(a, slut, tblk, blockIdx.x - blocks_b, gridDim.x - blocks_b);
+}
+
 // ---------------------------------------------------------------------------
 // Encoder for a wide encoding (int16 inputs in [xmin, xmin + nvalues)): the
 // same brick production from a table of up to 4096 packed codes.  The table
 // is too large for kernel arguments; it lives in a device array (one per side,
 // uploaded once per device) and each workgroup stages it into LDS, then walks
-// several bricks per wave to spread that load.
+// several bricks per wave to spread that load.  Brick order as the byte encoder's; the B side
+// transposes its 64 x 32 block through LDS as 16-bit pairs of rows (it gathered single entries
+// with stride N before: 49 us at 2048^2, and the A side packed its planes nibble by nibble).
 // ---------------------------------------------------------------------------
+constexpr int kTileCol16 = 144;  // bytes per column: 64 int16 rows and 16 bytes of padding
+
 template <bool kTransposed>
-__global__ __launch_bounds__(256) void encode16_kernel(const int16_t* __restrict__ x, int64_t rows,
-                                                       int64_t K, int64_t ld, int64_t KS, int64_t R32,
-                                                       int64_t nbricks, int nplanes,
-                                                       uint8_t* __restrict__ planes, int64_t plane_stride,
-                                                       int32_t* flag, int side, int32_t xmin,
-                                                       int32_t nvalues) {
-  __shared__ uint32_t slut[kWideValues];
-  for (int i = threadIdx.x; i < nvalues; i += blockDim.x) slut[i] = g_wide_lut[side][i];
-  __syncthreads();
+__device__ __forceinline__ void encode16_side(const EncodeArgs& a, const uint32_t* slut, uint8_t* tblk, int32_t xmin,
+                                              int32_t nvalues, unsigned block, unsigned blocks) {
+  const int16_t* __restrict__ x = reinterpret_cast<const int16_t*>(a.x);
   const int lane = threadIdx.x & 63;
-  auto look = [&](int v) -> uint32_t {
-    const uint32_t i = (uint32_t)(v - xmin);
+  auto look = [&](uint32_t half) -> uint32_t {  // half: the entry in the low 16 bits
+    const uint32_t i = (uint32_t)((int)(int16_t)half - xmin);
     return i < (uint32_t)nvalues ? slut[i] : kLutInvalid;
   };
   uint32_t bad = 0;
-  for (int64_t brick = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); brick < nbricks;
-       brick += (int64_t)gridDim.x * 4) {
-    const int64_t rb = brick / KS, ks = brick - rb * KS;
+  for (int64_t brick = (int64_t)block * 4 + (threadIdx.x >> 6); brick < a.nbricks; brick += (int64_t)blocks * 4) {
+    int64_t rb, ks;
+    if (kTransposed) {
+      const int64_t q = brick >> 2, groups = (a.R32 + 3) / 4;
+      ks = q / groups;
+      rb = (q - ks * groups) * 4 + (brick & 3);
+      if (rb >= a.R32) continue;
+    } else {
+      rb = brick / a.KS;
+      ks = brick - rb * a.KS;
+    }
     const int64_t row = rb * kBrickRows + (lane & 31);
     const int64_t k0 = ks * kBrickK + (lane >> 5) * 32;
-    const bool row_ok = row < rows;
+    const bool row_ok = row < a.rows;
     uint32_t e[32];
     if (!kTransposed) {
-      const int16_t* src = x + row * ld + k0;
-      if (row_ok && k0 + 32 <= K && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
+      const int16_t* src = x + row * a.ld + k0;
+      if (row_ok && k0 + 32 <= a.K) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const uint4 w = *reinterpret_cast<const uint4*>(src + 8 * q);
-          const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+          const Any16 w = *reinterpret_cast<const Any16*>(src + 8 * q);
 #pragma unroll
-          for (int j = 0; j < 8; ++j) e[8 * q + j] = look((int16_t)(ws[j >> 1] >> (16 * (j & 1))));
+          for (int j = 0; j < 8; ++j) e[8 * q + j] = look(w.w[j >> 1] >> (16 * (j & 1)));
         }
       } else {
 #pragma unroll
-        for (int j = 0; j < 32; ++j) e[j] = (row_ok && k0 + j < K) ? look(src[j]) : 0u;
+        for (int j = 0; j < 32; ++j) e[j] = 0u;
+        if (row_ok && k0 < a.K) {
+#pragma unroll
+          for (int j = 0; j < 32; ++j)
+            if (k0 + j < a.K) e[j] = look((uint16_t)src[j]);
+        }
       }
     } else {
+      // Lane l takes columns 8 (l & 3) .. +7 of block rows 2 (l >> 2), +1 and those 32 rows below, and
+      // writes each column's two rows as one word.
+      uint8_t* tw = tblk + (threadIdx.x >> 6) * (32 * kTileCol16);
+      const int64_t n0 = rb * kBrickRows;
+      const int c0 = 8 * (lane & 3);
 #pragma unroll
-      for (int j = 0; j < 32; ++j) e[j] = (row_ok && k0 + j < K) ? look(x[(k0 + j) * ld + row]) : 0u;
+      for (int h = 0; h < 2; ++h) {
+        const int r0 = 32 * h + 2 * (lane >> 2);
+        const int64_t kr = ks * kBrickK + r0;
+        const int16_t* src = x + kr * a.ld + n0 + c0;
+        Any16 u[2];
+        if (n0 + 32 <= a.rows && kr + 2 <= a.K) {
+          u[0] = *reinterpret_cast<const Any16*>(src);
+          u[1] = *reinterpret_cast<const Any16*>(src + a.ld);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) u[i].w[c] = 0;
+            if (kr + i < a.K)
+#pragma unroll
+              for (int c = 0; c < 8; ++c)
+                if (n0 + c0 + c < a.rows) u[i].w[c >> 1] |= (uint32_t)(uint16_t)src[i * a.ld + c] << (16 * (c & 1));
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          // v_perm_b32: the low (high) halves of both rows
+          const uint32_t lo = __builtin_amdgcn_perm(u[1].w[c], u[0].w[c], 0x05040100u);
+          const uint32_t hi = __builtin_amdgcn_perm(u[1].w[c], u[0].w[c], 0x07060302u);
+          *reinterpret_cast<uint32_t*>(tw + (c0 + 2 * c) * kTileCol16 + 2 * r0) = lo;
+          *reinterpret_cast<uint32_t*>(tw + (c0 + 2 * c + 1) * kTileCol16 + 2 * r0) = hi;
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS writes are done
+      __builtin_amdgcn_wave_barrier();
+      const uint8_t* col = tw + (lane & 31) * kTileCol16 + (lane >> 5) * 64;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint4 w = *reinterpret_cast<const uint4*>(col + 16 * q);
+        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          e[8 * q + j] = (row_ok && k0 + 8 * q + j < a.K) ? look(ws[j >> 1] >> (16 * (j & 1))) : 0u;
+      }
+      __builtin_amdgcn_wave_barrier();
     }
 #pragma unroll
     for (int j = 0; j < 32; ++j) bad |= e[j];
-    uint8_t* dst = planes + (ks * R32 + rb) * kBrickBytes + lane * 16;
-    for (int p = 0; p < nplanes; ++p) {
-      uint32_t d[4] = {0, 0, 0, 0};
+    uint8_t* dst = a.planes + (ks * a.R32 + rb) * kBrickBytes + lane * 16;
+    uint32_t d[6][4];
+    pack_e2m1_planes<6>(e, d);
 #pragma unroll
-      for (int j = 0; j < 32; ++j) d[j >> 3] |= ((e[j] >> (4 * p)) & 0xfu) << (4 * (j & 7));
-      *reinterpret_cast<uint4*>(dst + p * plane_stride) = make_uint4(d[0], d[1], d[2], d[3]);
+    for (int p = 0; p < 6; ++p) {
+      if (p >= a.nplanes) break;
+      *reinterpret_cast<uint4*>(dst + p * a.plane_stride) = make_uint4(d[p][0], d[p][1], d[p][2], d[p][3]);
     }
   }
-  if ((bad & kLutInvalid) && flag != nullptr) atomicOr(flag, 1);
+  if ((bad & kLutInvalid) && a.flag != nullptr) atomicOr(a.flag, 1);
+}
+
+// The two sides of a wide product: blocks_b workgroups for B, the rest for A (either may have none).
+__global__ __launch_bounds__(256) void encode16_kernel(EncodeArgs a, EncodeArgs b, unsigned blocks_b, int32_t xmin_a,
+                                                       int32_t nvalues_a, int32_t xmin_b, int32_t nvalues_b) {
+  __shared__ uint32_t slut[kWideValues];
+  __shared__ __attribute__((aligned(16))) uint8_t tblk[4 * 32 * kTileCol16];
+  const bool side_b = blockIdx.x < blocks_b;
+  const int nvalues = side_b ? nvalues_b : nvalues_a;
+  const uint32_t* lut = g_wide_lut[side_b ? 1 : 0];
+  for (int i = threadIdx.x; i < nvalues; i += blockDim.x) slut[i] = lut[i];
+  __syncthreads();
+  if (side_b)
+    encode16_side<true>(b, slut, tblk, xmin_b, nvalues_b, blockIdx.x, blocks_b);
+  else
+    encode16_side<false>(a, slut, tblk, xmin_a, nvalues_a, blockIdx.x - blocks_b, gridDim.x - blocks_b);
 }
 
 // ---------------------------------------------------------------------------
@@ -1483,52 +1617,66 @@ awe_status noalloc_planes(void** out) {
   return AWE_OK;
 }
 
-awe_status launch_encode(const EncodeLaunch& e, hipStream_t stream) {
+namespace {
+// Kernel arguments and workgroups of one side (none for an empty one).
+unsigned encode_args(const EncodeLaunch& e, EncodeArgs& a) {
   const int64_t rb = (e.rows + kBrickRows - 1) / kBrickRows;
-  const int64_t kp = (e.K + kKPad - 1) / kKPad * kKPad;
-  const int64_t KS = kp / kBrickK;
-  const int64_t nbricks = rb * KS;
-  if (nbricks == 0) return AWE_OK;
-  if (e.wide) {
-    awe_status st = ensure_wide_table(e);
-    if (st != AWE_OK) return st;
-    const int64_t blocks = std::min<int64_t>((nbricks + 15) / 16, 4096);
-    const int16_t* x = reinterpret_cast<const int16_t*>(e.x);
-    if (e.transposed)
-      hipLaunchKernelGGL(encode16_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, x, e.rows,
-                         e.K, e.ld, KS, rb, nbricks, e.nplanes, e.planes, e.plane_stride, e.flag, e.side,
-                         e.xmin, e.nvalues);
-    else
-      hipLaunchKernelGGL(encode16_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, x, e.rows,
-                         e.K, e.ld, KS, rb, nbricks, e.nplanes, e.planes, e.plane_stride, e.flag, e.side,
-                         e.xmin, e.nvalues);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) {
-      set_error(std::string("encode launch: ") + hipGetErrorString(err));
-      return AWE_ERR_HIP;
-    }
-    return AWE_OK;
-  }
-  LutArg lut;
-  for (int i = 0; i < 256; ++i) lut.v[i] = e.lut[i];
-  // one brick per wave; past 2^31 - 1 workgroups the waves walk several bricks each (the B
-  // side in groups of four column blocks, the last group padded)
-  const int64_t nb = e.transposed ? (rb + 3) / 4 * 4 * KS : nbricks;
-  const int64_t blocks = std::min<int64_t>((nb + 3) / 4, 0x7fffffffLL);
-  if (e.transposed)
-    hipLaunchKernelGGL(encode_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                       reinterpret_cast<const uint8_t*>(e.x), e.rows, e.K, e.ld, KS, rb, nb,
-                       e.nplanes, e.nplanes8, e.fp6, e.planes, e.plane_stride, e.flag, lut);
-  else
-    hipLaunchKernelGGL(encode_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                       reinterpret_cast<const uint8_t*>(e.x), e.rows, e.K, e.ld, KS, rb, nbricks,
-                       e.nplanes, e.nplanes8, e.fp6, e.planes, e.plane_stride, e.flag, lut);
-  hipError_t err = hipGetLastError();
+  a.x = reinterpret_cast<const uint8_t*>(e.x);
+  a.rows = e.rows;
+  a.K = e.K;
+  a.ld = e.ld;
+  a.KS = (e.K + kKPad - 1) / kKPad * kKPad / kBrickK;
+  a.R32 = rb;
+  // one brick per wave (the B side in groups of four column blocks, the last group padded); past
+  // 2^23 workgroups the waves walk several bricks each.  A wide encoding's workgroups stage 16 KiB
+  // of table each: past 2048 of them (8 per CU) their waves walk several bricks.
+  a.nbricks = e.transposed ? (rb + 3) / 4 * 4 * a.KS : rb * a.KS;
+  a.nplanes = e.nplanes;
+  a.nplanes8 = e.nplanes8;
+  a.fp6 = e.fp6;
+  a.planes = e.planes;
+  a.plane_stride = e.plane_stride;
+  a.flag = e.flag;
+  return (unsigned)std::min<int64_t>((a.nbricks + 3) / 4, e.wide ? 2048 : (int64_t(1) << 23));
+}
+
+awe_status encode_launched() {
+  const hipError_t err = hipGetLastError();
   if (err != hipSuccess) {
     set_error(std::string("encode launch: ") + hipGetErrorString(err));
     return AWE_ERR_HIP;
   }
   return AWE_OK;
+}
+}  // namespace
+
+awe_status launch_encode(const EncodeLaunch& e, hipStream_t stream) {
+  const EncodeLaunch* o = e.other;  // the other side of the product, or null
+  EncodeArgs ea{}, eb{};
+  const EncodeLaunch* sa = !e.transposed ? &e : o;
+  const EncodeLaunch* sb = e.transposed ? &e : o;
+  const unsigned na = sa ? encode_args(*sa, ea) : 0, nb = sb ? encode_args(*sb, eb) : 0;
+  if (na + nb == 0) return AWE_OK;
+  if (e.wide) {
+    for (const EncodeLaunch* s : {sa, sb}) {
+      if (!s) continue;
+      const awe_status st = ensure_wide_table(*s);
+      if (st != AWE_OK) return st;
+    }
+    hipLaunchKernelGGL(encode16_kernel, dim3(na + nb), dim3(256), 0, stream, ea, eb, nb, sa ? sa->xmin : 0,
+                       sa ? sa->nvalues : 0, sb ? sb->xmin : 0, sb ? sb->nvalues : 0);
+    return encode_launched();
+  }
+  LutArg la, lb;
+  if (na) std::copy(sa->lut, sa->lut + 256, la.v);
+  if (nb) std::copy(sb->lut, sb->lut + 256, lb.v);
+  if (na && nb)
+    hipLaunchKernelGGL(encode_pair_kernel, dim3(na + nb), dim3(256), 0, stream, ea, eb, nb, la, lb);
+  else if (nb)
+    hipLaunchKernelGGL(encode_kernel<true>, dim3(nb), dim3(256), 0, stream, eb, lb);
+  else
+    hipLaunchKernelGGL(encode_kernel<false>, dim3(na), dim3(256), 0, stream, ea, la);
+  return encode_launched();
 }
 
 awe_status launch_gemm(const GemmLaunch& L, hipStream_t stream) {

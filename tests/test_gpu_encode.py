@@ -84,3 +84,29 @@ def test_encode_wide_range_flag():
     A[8, 8] = 2048
     _encode(awe.ENC_FP16, 0, awe.SIDE_A, A, 32, 64, flag)
     assert int(flag.item()) != 0
+
+
+@pytest.mark.parametrize("name", ["awe6", "awe4", "fp16_12", "fp6p4"])
+@pytest.mark.parametrize("rows,K,pad,offset", [(33, 65, 3, 1), (130, 190, 0, 5), (64, 128, 1, 8)])
+def test_encode_at_any_alignment(name, rows, K, pad, offset):
+    # rows that start at any address: an odd leading dimension and a base pointer inside a buffer;
+    # the bytes around the operand are out of range values that must not be read into the planes
+    s = sc.ALL_SCHEMES[name]()
+    for side, shape, rng_s, tag in ((awe.SIDE_A, (rows, K), s.range_a, "a"), (awe.SIDE_B, (K, rows), s.range_b, "b")):
+        dt = _dtype(*rng_s)
+        X = inputs.uniform(np.random.default_rng(rows + K), shape, *rng_s, dtype=dt)
+        ld = shape[1] + pad
+        buf = np.full(offset + shape[0] * ld + 64, np.iinfo(dt).max, dt)
+        for i in range(shape[0]):
+            buf[offset + i * ld: offset + i * ld + shape[1]] = X[i]
+        info = awe.get_encoding_info(EXACT[name])
+        npl = info["planes_a"] if side == awe.SIDE_A else info["planes_b"]
+        planes = torch.full((awe.plane_bytes(EXACT[name], 0, side, rows, K),), 0xAB, dtype=torch.uint8, device="cuda")
+        d = to_dev(buf)
+        flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+        awe.encode(EXACT[name], 0, side, d.data_ptr() + offset * buf.itemsize, rows, K, ld, planes, flag)
+        torch.cuda.synchronize()
+        assert flag.item() == 0
+        got = decode_planes(planes.cpu().numpy(), npl, rows, K, info["formats_a" if side == awe.SIDE_A else "formats_b"])
+        want = sc.encode_planes(s, tag, X)
+        assert np.array_equal(got, want if side == awe.SIDE_A else np.swapaxes(want, 1, 2)), side
