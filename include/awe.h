@@ -25,8 +25,8 @@
  *  - awe_encode, awe_gemm_planes, awe_gemm_exact and awe_gemm_mod enqueue only kernels (no
  *    memset, no copy), so they can be captured into a HIP graph once each has been called
  *    eagerly on the device (the first calls set the GEMM's LDS limit and, for the FP16
- *    scheme, upload its code table).  awe_gemm_crt also copies host tables and is not meant
- *    for capture.
+ *    scheme, upload its code table).  awe_gemm_crt uploads the code tables of its moduli the
+ *    first time it meets them on a device, so the same holds for it, modulus by modulus.
  *  - Matrices are row-major: A is M x K (A[i*lda + k]), B is K x N
  *    (B[k*ldb + j]), C is M x N (C[i*ldc + j]).  Leading dimensions must be
  *    at least the row length.  Empty problems (M or N zero) succeed and write
@@ -264,9 +264,9 @@ awe_status awe_crt_workspace_bytes(const int32_t* moduli, int32_t n, int64_t M, 
    awe_gemm_mod for every modulus (all moduli in one kernel launch where the tile configuration
    allows it), awe_crt into c128 and/or c64 (as for awe_crt, leading dimension ldc).  Requires M_prod > 2 K bound_a bound_b (AWE_ERR_OVERFLOW otherwise) and every
    modulus to have a scheme (AWE_ERR_UNSUPPORTED).  Entries beyond their bound set
-   *d_range_flag.  The workspace (caller-owned device memory, awe_crt_workspace_bytes) holds the
-   moduli's code tables, all their planes and the n residue products (one byte per output each:
-   every modulus is at most 256); it is uploaded to and written on `stream`. */
+   *d_range_flag.  The workspace (caller-owned device memory, awe_crt_workspace_bytes) holds all
+   the moduli's planes and the n residue products (one byte per output each: every modulus is
+   at most 256); it is written on `stream`. */
 awe_status awe_gemm_crt(int64_t M, int64_t N, int64_t K, const int64_t* A, int64_t lda,
                         const int64_t* B, int64_t ldb, int64_t bound_a, int64_t bound_b,
                         const int32_t* moduli, int32_t n, int64_t* c128, double* c64, int64_t ldc,

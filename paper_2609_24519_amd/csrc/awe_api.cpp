@@ -406,14 +406,11 @@ awe_status rns_setup(const int32_t* moduli, int32_t n, ResidueParams* rp, CrtPar
       const uint32_t m = (uint32_t)moduli[j];
       cp->mod[j].m = m;
       cp->mod[j].inv = 1.0f / (float)m;
-      uint64_t pj = 1;  // m_0 ... m_{j-1} mod m
-      for (int i = 0; i < j; ++i) {
-        cp->c[j][i] = (uint8_t)pj;
-        pj = pj * (uint32_t)moduli[i] % m;
-      }
-      cp->mod[j].d = inverse_mod((uint32_t)pj, m);
-      const uint32_t most = (uint32_t)(kMaxModuli - 1) * 255u * 255u;  // largest subtracted sum
-      cp->mod[j].off = (most / m + 1) * m;
+      uint32_t p[kMaxModuli + 1] = {1 % m};  // m_0 ... m_{i-1} mod m
+      for (int i = 0; i < j; ++i) p[i + 1] = p[i] * (uint32_t)moduli[i] % m;
+      const uint32_t d = inverse_mod(p[j], m);
+      cp->mod[j].d = d;
+      for (int i = 0; i < j; ++i) cp->c[j][i] = (uint8_t)((m - p[i] * d % m) % m);
     }
     cp->M_lo = (uint64_t)M;
     cp->M_hi = (uint64_t)(M >> 64);
@@ -451,30 +448,6 @@ CrtLayout crt_layout(const int32_t* moduli, int32_t n, int64_t M, int64_t N, int
   L.res_c = (size_t)round_up((int64_t)n * M * N, 256);
   L.total = L.luts + L.planes_a + L.planes_b + L.res_c;
   return L;
-}
-
-// The code tables of a set of moduli packed for the device (A side, then B side), built once
-// per set and kept for the life of the process, so that an asynchronous copy may read them.
-const std::vector<uint32_t>* crt_tables(const int32_t* moduli, int32_t n, awe_status* st) {
-  static std::mutex mu;
-  static std::map<std::vector<int32_t>, std::unique_ptr<std::vector<uint32_t>>> cache;
-  std::vector<int32_t> key(moduli, moduli + n);
-  {
-    std::lock_guard<std::mutex> lk(mu);
-    auto it = cache.find(key);
-    if (it != cache.end()) return it->second.get();
-  }
-  auto t = std::make_unique<std::vector<uint32_t>>(2 * (size_t)n * 256);
-  for (int j = 0; j < n; ++j) {
-    const Scheme* s = scheme_or_fail(AWE_ENC_MOD, moduli[j], st);
-    if (!s) return nullptr;
-    std::copy(s->lut_a.begin(), s->lut_a.begin() + 256, t->begin() + (size_t)j * 256);
-    std::copy(s->lut_b.begin(), s->lut_b.begin() + 256, t->begin() + ((size_t)n + j) * 256);
-  }
-  std::lock_guard<std::mutex> lk(mu);
-  auto& slot = cache[key];
-  if (!slot) slot = std::move(t);
-  return slot.get();
 }
 
 }  // namespace
@@ -705,42 +678,38 @@ awe_status awe_gemm_crt(int64_t M, int64_t N, int64_t K, const int64_t* A, int64
   if (L.total > 0 && (workspace == nullptr || ws_bytes < L.total))
     return fail(AWE_ERR_WORKSPACE, "workspace smaller than awe_crt_workspace_bytes");
   uint8_t* ws = reinterpret_cast<uint8_t*>(workspace);
-  uint32_t* luts = reinterpret_cast<uint32_t*>(ws);
   uint8_t* pla = ws + L.luts;
   uint8_t* plb = pla + L.planes_a;
   uint8_t* rc = plb + L.planes_b;
   if (K > 0) {
-    // every modulus's planes of A and of B straight from the int64 operands
-    const std::vector<uint32_t>* tab = crt_tables(moduli, n, &st);
-    if (!tab) return st;
-    hipError_t err = hipMemcpyAsync(luts, tab->data(), tab->size() * sizeof(uint32_t),
-                                    hipMemcpyHostToDevice, stream);
-    if (err != hipSuccess) return fail(AWE_ERR_HIP, std::string("table upload: ") + hipGetErrorString(err));
+    // every modulus's planes of A and of B straight from the int64 operands, in one launch
     const int64_t kp = round_up(K, kKPad);
+    ResidueEncodeArgs e[2] = {};
     for (int side = 0; side < 2; ++side) {
       const bool sideA = side == 0;
-      ResidueEncodeArgs e{};
-      e.x = sideA ? A : B;
-      e.rows = sideA ? M : N;
-      e.K = K;
-      e.ld = sideA ? lda : ldb;
-      e.KS = kp / kBrickK;
-      e.R32 = (e.rows + kBrickRows - 1) / kBrickRows;
-      e.nbricks = e.R32 * e.KS;
-      e.bound = sideA ? bound_a : bound_b;
-      e.luts = luts + (sideA ? 0 : (size_t)n * 256);
-      e.planes = sideA ? pla : plb;
-      e.plane_stride = plane_stride_bytes(e.rows, K);
+      ResidueEncodeArgs& r = e[side];
+      r.x = sideA ? A : B;
+      r.rows = sideA ? M : N;
+      r.K = K;
+      r.ld = sideA ? lda : ldb;
+      r.KS = kp / kBrickK;
+      r.R32 = (r.rows + kBrickRows - 1) / kBrickRows;
+      r.nbricks = r.R32 * r.KS;
+      r.bound = sideA ? bound_a : bound_b;
+      r.planes = sideA ? pla : plb;
+      r.plane_stride = plane_stride_bytes(r.rows, K);
       for (int j = 0; j < n; ++j) {
         const Scheme* s = scheme_or_fail(AWE_ENC_MOD, moduli[j], &st);
         if (!s) return st;
-        e.off[j] = sideA ? L.off_a[j] : L.off_b[j];
-        e.np[j] = sideA ? s->na : s->nb;
+        r.off[j] = sideA ? L.off_a[j] : L.off_b[j];
+        r.np[j] = sideA ? s->na : s->nb;
+        r.luts[j] = (sideA ? s->lut_a : s->lut_b).data();
       }
-      e.flag = d_range_flag;
-      st = launch_residue_encode(e, rp, !sideA, stream);
-      if (st != AWE_OK) return st;
+      r.flag = d_range_flag;
     }
+    e[0].other = &e[1];
+    st = launch_residue_encode(e[0], rp, false, stream);
+    if (st != AWE_OK) return st;
   }
   // the n mod-m GEMMs: one grouped launch when each is a single launch (AWE_GEMM_GROUPED=0
   // asks for one launch per modulus)

@@ -209,6 +209,16 @@ struct Slice {
 // The variant that suits a launch, if it beats the tile configurations' `tile_us` on `cus` CUs.
 Slice choose_slice(const GemmLaunch& L, int cus, double tile_us);
 awe_status launch_slice(const GemmLaunch& L, Slice s, hipStream_t stream);
+// The same for launches that share one (launch_gemm_group's; order: the jobs' order).
+int choose_slice_group(const GemmLaunch* L, int n, int cus, double tile_us);
+awe_status launch_slice_group(const GemmLaunch* L, const int* order, int n, int variant, hipStream_t stream);
+// Time of a grouped launch (us): each job has `tiles` tiles, the jobs' tile times add up to `sum`, the
+// longest is `longest`.  Many jobs fill the rounds, so they are not quantised: the CUs' share and a
+// third of a tile for the ragged end, but no less than one tile.
+inline double group_time(double sum, double longest, int64_t tiles, int cus) {
+  const double share = sum * (double)tiles / cus + 0.3 * longest;
+  return 4.0 + (share > longest ? share : longest);
+}
 
 // Raises a kernel's dynamic LDS limit to `bytes` once per device (`done`, guarded by `mu`).
 awe_status set_lds_limit(const void* fn, int bytes, std::mutex& mu, std::set<int>& done);
@@ -236,12 +246,13 @@ struct ResidueEncodeArgs {
   int64_t rows, K, ld;        // A side: x[row * ld + k]; B side: x[k * ld + row]
   int64_t KS, R32, nbricks;   // bricks along K per row block, row blocks, all bricks
   int64_t bound;              // |x| above it sets *flag
-  const uint32_t* luts;       // device: n x 256 packed E2M1 codes, one table per modulus
+  const uint32_t* luts[kMaxModuli];  // host: modulus j's packed E2M1 codes of residues 0 .. m - 1
   uint8_t* planes;            // modulus j's planes at planes + off[j], plane_stride apart
   int64_t plane_stride;
   int64_t off[kMaxModuli];
   int32_t np[kMaxModuli];
   int32_t* flag;
+  const ResidueEncodeArgs* other;  // the other operand of the product, in the same launch (nullable)
 };
 awe_status launch_residue_encode(const ResidueEncodeArgs& a, const ResidueParams& P, bool transposed,
                                  hipStream_t stream);
@@ -250,10 +261,11 @@ struct CrtModulus {
   uint32_t m;
   float inv;     // 1/m in fp32
   uint32_t d;    // (m_0 ... m_{j-1})^-1 mod m_j
-  uint32_t off;  // multiple of m_j above any subtracted digit sum
+  uint32_t unused;
 };
 struct alignas(16) CrtParams {
-  uint8_t c[kMaxModuli][kMaxModuli];  // c[j][i] = (m_0 ... m_{i-1}) mod m_j, i < j (row j: digit j's)
+  // c[j][i] = -(m_0 ... m_{i-1}) d_j mod m_j for i < j, zero from i = j on (row j: digit j's)
+  uint8_t c[kMaxModuli][kMaxModuli];
   CrtModulus mod[kMaxModuli];
   uint64_t M_lo, M_hi;          // M = m_0 ... m_{n-1} < 2^127
   uint64_t half_lo, half_hi;    // floor(M / 2)

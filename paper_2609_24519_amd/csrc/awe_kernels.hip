@@ -58,18 +58,6 @@ struct __attribute__((packed)) Any8 {
   uint32_t w[2];
 };
 
-// The 4 x 4 byte transpose of v (v[i] holds bytes 0 .. 3 of row i): out[j] holds byte j of rows 0 .. 3.
-__device__ __forceinline__ void transpose4x4(const uint32_t (&v)[4], uint32_t (&out)[4]) {
-  const uint32_t t0 = __builtin_amdgcn_perm(v[1], v[0], 0x05010400u);
-  const uint32_t t1 = __builtin_amdgcn_perm(v[1], v[0], 0x07030602u);
-  const uint32_t t2 = __builtin_amdgcn_perm(v[3], v[2], 0x05010400u);
-  const uint32_t t3 = __builtin_amdgcn_perm(v[3], v[2], 0x07030602u);
-  out[0] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
-  out[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
-  out[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
-  out[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
-}
-
 // B side: a wave's 64 x 32 input block lies column-major in LDS, kTileCol bytes per column (64 rows +
 // 16 bytes of padding, so that the 16-byte column reads hit distinct banks).
 constexpr int kTileCol = 80;
@@ -616,36 +604,30 @@ __device__ __forceinline__ void store_value(const GemmArgs& g, int row, int col,
 }
 
 __device__ __forceinline__ void store_output(const GemmArgs& g, int row, int col, int32_t val) {
-  if (g.modulus) {
-    if (row >= g.M || col >= g.N) return;
-    const int64_t off = (int64_t)row * g.ldc + col;
-    const int32_t m = g.modulus;
-    int32_t rr = val % m;
-    if (rr < 0) rr += m;
-    int32_t* Cp = reinterpret_cast<int32_t*>(g.C);
-    if (g.accumulate)
-      Cp[off] = (Cp[off] + rr) % m;
-    else
-      __builtin_nontemporal_store(rr, Cp + off);
-    return;
-  }
   store_value(g, row, col, (int64_t)(val >> g.log2D) * g.outer);
 }
 
-// A residue written as a byte (C's elements are bytes: m <= 256).  Its own epilogue loop, so
+// A residue, as int32 or (store_residue_u8) as a byte: m <= 256.  Their own epilogue loops, so
 // that the int32 / int64 one keeps its size (a larger loop body stopped its unrolling).
-__device__ __forceinline__ void store_residue_u8(const GemmArgs& g, int row, int col, int32_t val) {
+__device__ __forceinline__ void store_residue(const GemmArgs& g, int row, int col, int32_t rr) {
   if (row >= g.M || col >= g.N) return;
-  const int64_t off = (int64_t)row * g.ldc + col;
-  const int32_t m = g.modulus;
-  int32_t rr = val % m;
-  if (rr < 0) rr += m;
-  uint8_t* Cb = reinterpret_cast<uint8_t*>(g.C);
+  int32_t* Cp = reinterpret_cast<int32_t*>(g.C) + ((int64_t)row * g.ldc + col);
   if (g.accumulate) {
-    const int32_t s = Cb[off] + rr;
-    Cb[off] = (uint8_t)(s >= m ? s - m : s);
+    const int32_t s = *Cp + rr;
+    *Cp = s >= g.modulus ? s - g.modulus : s;
   } else {
-    __builtin_nontemporal_store((uint8_t)rr, Cb + off);
+    __builtin_nontemporal_store(rr, Cp);
+  }
+}
+
+__device__ __forceinline__ void store_residue_u8(const GemmArgs& g, int row, int col, int32_t rr) {
+  if (row >= g.M || col >= g.N) return;
+  uint8_t* Cb = reinterpret_cast<uint8_t*>(g.C) + ((int64_t)row * g.ldc + col);
+  if (g.accumulate) {
+    const int32_t s = *Cb + rr;
+    *Cb = (uint8_t)(s >= g.modulus ? s - g.modulus : s);
+  } else {
+    __builtin_nontemporal_store((uint8_t)rr, Cb);
   }
 }
 
@@ -1161,18 +1143,25 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
         }
     return;
   }
-  if (g.c64 == 2) {  // residues as bytes (only with a modulus, whose tiles are never split)
-    auto emit8 = [&](int i, int j, int v, int32_t val) {
-      store_residue_u8(g, row0 + i * BS + (BS == 16 ? v : 8 * (v >> 2) + (v & 3)), col0 + j * BS, val);
+  if (g.modulus) {  // residues, whose tiles are never split
+    const ModReducer mod(g.modulus);
+    auto residues = [&](auto store) {
+      auto emit_r = [&](int i, int j, int v, int32_t val) {
+        store(row0 + i * BS + (BS == 16 ? v : 8 * (v >> 2) + (v & 3)), col0 + j * BS, mod(val));
+      };
+#pragma unroll
+      for (int b = 0; b < NREG; ++b)
+#pragma unroll
+        for (int v = 0; v < C::AV; ++v) emit_r(b / C::AN, b % C::AN, v, iacc[b / C::AN][b % C::AN][v]);
+#pragma unroll
+      for (int b = NREG; b < C::AM * C::AN; ++b)
+#pragma unroll
+        for (int v = 0; v < C::AV; ++v) emit_r(b / C::AN, b % C::AN, v, fold_lds[((b - NREG) * C::AV + v) * 64]);
     };
-#pragma unroll
-    for (int b = 0; b < NREG; ++b)
-#pragma unroll
-      for (int v = 0; v < C::AV; ++v) emit8(b / C::AN, b % C::AN, v, iacc[b / C::AN][b % C::AN][v]);
-#pragma unroll
-    for (int b = NREG; b < C::AM * C::AN; ++b)
-#pragma unroll
-      for (int v = 0; v < C::AV; ++v) emit8(b / C::AN, b % C::AN, v, fold_lds[((b - NREG) * C::AV + v) * 64]);
+    if (g.c64 == 2)
+      residues([&](int row, int col, int32_t rr) { store_residue_u8(g, row, col, rr); });
+    else
+      residues([&](int row, int col, int32_t rr) { store_residue(g, row, col, rr); });
     return;
   }
 #pragma unroll
@@ -1354,24 +1343,31 @@ Choice choose_cfg(const GemmLaunch& L) {
   return t192 < 0.97 * t128 ? Choice{6, t192} : Choice{5, t128};
 }
 
-// Tile configuration of a grouped launch of n jobs of one shape: AWE_GEMM_CFG if set, else 5
-// or 16 (256 x 128 or 256 x 256, the latter on config 16's schedule), whichever a per-round model
-// fitted to configs 5 and 13 gives less time summed over the jobs' tiles (many jobs fill the
-// rounds, so the rounds are not quantised); config 16 runs the residue route's grouped GEMM at
-// 4096 x 4096 x 16384 about 4 % faster than 13.
-int choose_group_cfg(const GemmLaunch* L, int n) {
+// Tile configuration of a grouped launch of n jobs of one shape and its estimated time (us):
+// AWE_GEMM_CFG if set, else 5 or 16 (256 x 128 or 256 x 256, the latter on config 16's schedule),
+// whichever the tiles' times (the slopes of choose_cfg, fixed parts that order awe_gemm_crt at 1024^2 x
+// 4096, 2048^3 and 512^2 x 8192 with 23 moduli as measured) give less of.
+struct GroupChoice {
+  int cfg;
+  double us;
+};
+GroupChoice choose_group_cfg(const GemmLaunch* L, int n) {
   const char* e = getenv("AWE_GEMM_CFG");
   const int forced = e ? atoi(e) : -1;
-  if (forced >= 0) return forced;
-  const double tm = (double)((L[0].M + 255) / 256);
-  const double t128 = tm * (double)((L[0].N + 127) / 128), t256 = tm * (double)((L[0].N + 255) / 256);
-  double s128 = 0.0, s256 = 0.0;
+  if (forced >= 0) return GroupChoice{forced, 0.0};
+  const int cus = compute_units();
+  const int64_t tm = (L[0].M + 255) / 256, t128 = tm * ((L[0].N + 127) / 128), t256 = tm * ((L[0].N + 255) / 256);
+  double s128 = 0.0, s256 = 0.0, m128 = 0.0, m256 = 0.0;
   for (int j = 0; j < n; ++j) {
     const double k = (double)L[j].r * (double)(L[j].k_end - L[j].k_begin) / 6.0;
-    s128 += t128 * (2.2 * k + 1700.0);
-    s256 += t256 * (3.9 * k + 6000.0);
+    const double a = 0.0205 * k + 14.0, b = 0.0385 * k + 17.0;
+    s128 += a;
+    s256 += b;
+    m128 = std::max(m128, a);
+    m256 = std::max(m256, b);
   }
-  return s256 < s128 ? 16 : 5;
+  const double us128 = group_time(s128, m128, t128, cus), us256 = group_time(s256, m256, t256, cus);
+  return us256 < us128 ? GroupChoice{16, us256} : GroupChoice{5, us128};
 }
 
 // Tile configuration for E2M3 operands: AWE_GEMM_CFG_E2M3 (0: 256x128 with 8 waves in
@@ -1761,7 +1757,7 @@ bool group_cfg(int cfg) { return cfg == 1 || cfg == 4 || cfg == 5 || cfg == 13 |
 
 bool gemm_group_ok(const GemmLaunch* L, int n) {
   if (n < 1 || n > kMaxModuli) return false;
-  if (!group_cfg(choose_group_cfg(L, n))) return false;
+  if (!group_cfg(choose_group_cfg(L, n).cfg)) return false;
   for (int j = 0; j < n; ++j) {
     const GemmLaunch& a = L[j];
     if (a.fmt != kFmtE2M1 || a.shared || a.allpairs_a || a.accumulate || a.r < 1 || a.r > kGroupProducts)
@@ -1786,7 +1782,10 @@ awe_status launch_gemm_group(const GemmLaunch* L, int n, hipStream_t stream) {
   int order[kMaxModuli];
   for (int j = 0; j < n; ++j) order[j] = j;
   std::stable_sort(order, order + n, [&](int a, int b) { return L[a].r > L[b].r; });
-  switch (choose_group_cfg(L, n)) {
+  const GroupChoice tile = choose_group_cfg(L, n);
+  if (const int v = choose_slice_group(L, n, compute_units(), tile.us))
+    return launch_slice_group(L, order, n, v, stream);
+  switch (tile.cfg) {
     case 4: return launch_group_tile<Cfg8w64x64k4>(L, order, n, stream);
     case 5: return launch_group_tile<Cfg8w64x64k4p3>(L, order, n, stream);
     case 13: return launch_group_tile<Cfg8w64x128lf3>(L, order, n, stream);

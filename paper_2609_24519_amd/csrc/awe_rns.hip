@@ -5,7 +5,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <bitset>
 #include <cstdint>
+#include <map>
+#include <mutex>
+#include <string>
 #include <type_traits>
 
 #include "awe_internal.h"
@@ -141,130 +145,157 @@ __global__ __launch_bounds__(256) void residues_kernel(const int64_t* __restrict
   if (out_of_range && flag) *flag = 1;
 }
 
-// Residues of an int64 operand for every modulus, turned straight into each modulus's
-// stored E2M1 planes (Alg. 1's table lookup applied to the residue), without the dense
-// residue matrices in between.  One wave per brick of the plane layout, as the encoder:
-// lane L = 32 h + t produces row t of the brick at reduction indices 32 h .. 32 h + 31.
-// On the B side (x is K x N) lane l first loads reduction index ks*64 + l at 32 columns,
-// computes their residues and stages them in LDS, then reads its column back, per modulus.
-template <bool kTransposed>
-__global__ __launch_bounds__(256) void residue_encode_kernel(ResidueEncodeArgs a, ResidueParams P) {
-  __shared__ uint32_t slut[kMaxModuli * 256];
-  __shared__ uint8_t tblk[kTransposed ? 4 : 1][kTransposed ? 64 * 32 : 1];
-  const int n = P.n;
-  for (int i = threadIdx.x; i < n * 256; i += blockDim.x) slut[i] = a.luts[i];
-  __syncthreads();
+// ---------------------------------------------------------------------------
+// Residues of an int64 operand for every modulus, turned straight into each modulus's stored E2M1
+// planes (Alg. 1's table lookup applied to the residue), without the dense residue matrices in
+// between.  One wave per brick of the plane layout, as the encoder: lane L = 32 h + t produces row t
+// of the brick at reduction indices 32 h .. 32 h + 31 from that row's 32 entries, which it reads
+// itself: on the A side 256 consecutive bytes, on the B side (x is K x N) one entry of each of 32
+// rows, 256 bytes of a row per half wave, so nothing has to be transposed.
+//
+// Bound by its instructions (23 residues per entry), so a residue takes as few as possible.  With the
+// sign bit flipped an entry is the unsigned u = x + 2^63, eight bytes b_i, and
+// x = sum_i b_i (2^(8 i) mod m) - 2^63 (mod m): two four-way byte dot products onto the constant
+// (-2^63 mod m), t < 8 255^2 + 256 < 2^20.  One fused multiply-add with 2^23 leaves
+// q = round(t / m) in the low bits of a float (t 1/m is within 2^-4 / m of t / m), a 24-bit
+// multiply-add the remainder t - q m, within m / 2 + 1 of zero, and that indexes the modulus's table
+// directly, which is laid out for remainders -kLutHalf .. kLutHalf - 1.  Its entries hold one
+// plane's code per byte, so a pair of entries packs with one shift-or and four pairs with a byte
+// transpose.  1024 x 4096 and 4096 x 1024 entries, 23 moduli: 155 us for both operands with
+// double-precision reductions to [0, m) and codes packed nibble by nibble, 92 us now.
+// ---------------------------------------------------------------------------
+constexpr int kLutHalf = 136;  // remainders lie within 129
+constexpr int kLutSize = 2 * kLutHalf;
+
+// Per side and modulus (index m - 2): the table above, uploaded once per device.
+__device__ uint32_t g_mod_lut[2][255][kLutSize];
+
+struct ResidueSide {
+  const int64_t* x;
+  int64_t rows, K, ld, KS, R32, nbricks, bound;
+  uint8_t* planes;
+  int64_t plane_stride;
+  int64_t off[kMaxModuli];  // modulus j's planes at planes + off[j]
+  int32_t* flag;
+};
+struct ResidueModulus {
+  uint32_t m, w_lo, w_hi, init;  // w: 2^(8 i) mod m as bytes; init: -2^63 mod m
+  float inv;                     // 1/m
+  int32_t np[2];                 // planes on the A and the B side
+};
+struct ResidueArgs {
+  ResidueSide side[2];
+  ResidueModulus mod[kMaxModuli];
+  int32_t n, per_group;  // moduli, and moduli per workgroup (blockIdx.y)
+  unsigned blocks_a;     // workgroups of the A side; the rest are B's
+};
+
+template <int SIDE>
+__device__ __forceinline__ void residue_encode_side(const ResidueArgs& g, const uint32_t* slut, int j0, int j1,
+                                                    int64_t brick) {
+  const ResidueSide& a = g.side[SIDE];
+  if (brick >= a.nbricks) return;
   const int lane = threadIdx.x & 63;
-  bool out_of_range = false;
-  for (int64_t brick = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); brick < a.nbricks;
-       brick += (int64_t)gridDim.x * 4) {
-    const int64_t rb = brick / a.KS, ks = brick - rb * a.KS;
-    // this lane's 32 entries and which of them are real (the rest pad with code 0)
-    int64_t v[32];
-    uint32_t valid = 0;
-    if (!kTransposed) {
-      const int64_t row = rb * kBrickRows + (lane & 31), k0 = ks * kBrickK + (lane >> 5) * 32;
-      const int64_t* src = a.x + row * a.ld + k0;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) {
-        const bool ok = row < a.rows && k0 + e < a.K;
-        v[e] = ok ? src[e] : 0;
-        valid |= (ok ? 1u : 0u) << e;
-      }
-    } else {
-      const int64_t kr = ks * kBrickK + lane, n0 = rb * kBrickRows;
-      const int64_t* src = a.x + kr * a.ld + n0;
-#pragma unroll
-      for (int c = 0; c < 32; ++c) {
-        const bool ok = kr < a.K && n0 + c < a.rows;
-        v[c] = ok ? src[c] : 0;
-        valid |= (ok ? 1u : 0u) << c;
-      }
-    }
-    bool small = true;
+  int64_t rb, ks;
+  if (SIDE == 0) {
+    rb = brick / a.KS;
+    ks = brick - rb * a.KS;
+  } else {
+    ks = brick / a.R32;
+    rb = brick - ks * a.R32;
+  }
+  const int64_t row = rb * kBrickRows + (lane & 31), k0 = ks * kBrickK + (lane >> 5) * 32;
+  // entries past the operand read as 0, whose codes are 0
+  uint32_t lo[32], hi[32];
+  const int64_t* src = SIDE == 0 ? a.x + row * a.ld + k0 : a.x + k0 * a.ld + row;
+  if (row < a.rows && k0 + 32 <= a.K) {
 #pragma unroll
     for (int e = 0; e < 32; ++e) {
-      out_of_range |= v[e] > a.bound || v[e] < -a.bound;
-      small &= v[e] < (int64_t(1) << 53) && v[e] > -(int64_t(1) << 53);
+      const uint64_t v = (uint64_t)src[SIDE == 0 ? e : e * a.ld];
+      lo[e] = (uint32_t)v;
+      hi[e] = (uint32_t)(v >> 32);
     }
-    // one route for the whole wave (a per-entry choice would run both)
-    // Modulus j's planes of this brick from the lane's 32 residues r (this lane's row, or on
-    // the B side its row of K x N, transposed through LDS first).
-    auto emit = [&](int j, uint32_t (&r)[32]) {
-      uint32_t ok = valid;
-      if (kTransposed) {
-        uint8_t* tw = tblk[threadIdx.x >> 6];
-        uint32_t w[8] = {};
+  } else {
 #pragma unroll
-        for (int c = 0; c < 32; ++c) w[c >> 2] |= r[c] << (8 * (c & 3));
-        *reinterpret_cast<uint4*>(tw + lane * 32) = make_uint4(w[0], w[1], w[2], w[3]);
-        *reinterpret_cast<uint4*>(tw + lane * 32 + 16) = make_uint4(w[4], w[5], w[6], w[7]);
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS writes are done
-        __builtin_amdgcn_wave_barrier();
-        const uint8_t* col = tw + (lane >> 5) * 32 * 32 + (lane & 31);
-        const int64_t row = rb * kBrickRows + (lane & 31), k0 = ks * kBrickK + (lane >> 5) * 32;
-        ok = 0;
+    for (int e = 0; e < 32; ++e) lo[e] = hi[e] = 0;
+    if (row < a.rows && k0 < a.K) {
 #pragma unroll
-        for (int e = 0; e < 32; ++e) {
-          r[e] = col[e * 32];
-          ok |= (row < a.rows && k0 + e < a.K ? 1u : 0u) << e;
+      for (int e = 0; e < 32; ++e)
+        if (k0 + e < a.K) {
+          const uint64_t v = (uint64_t)src[SIDE == 0 ? e : e * a.ld];
+          lo[e] = (uint32_t)v;
+          hi[e] = (uint32_t)(v >> 32);
         }
-        __builtin_amdgcn_wave_barrier();
-      }
-      uint32_t code[32];
-#pragma unroll
-      for (int e = 0; e < 32; ++e) code[e] = ((ok >> e) & 1u) ? slut[j * 256 + r[e]] : 0u;
-      uint8_t* dst = a.planes + a.off[j] + (ks * a.R32 + rb) * kBrickBytes + lane * 16;
-      // the nibble transpose for exactly the planes the modulus has (1 to 3 for the mod-m
-      // schemes; up to 8 fit a code word)
-      auto store = [&](auto npc) {
-        constexpr int NP = decltype(npc)::value;
-        uint32_t d[NP][4];
-        pack_e2m1_planes<NP>(code, d);
-#pragma unroll
-        for (int pl = 0; pl < NP; ++pl) {
-          if (pl >= a.np[j]) break;
-          *reinterpret_cast<uint4*>(dst + pl * a.plane_stride) = make_uint4(d[pl][0], d[pl][1], d[pl][2], d[pl][3]);
-        }
-      };
-      const int np = a.np[j];
-      if (np == 1)
-        store(std::integral_constant<int, 1>{});
-      else if (np == 2)
-        store(std::integral_constant<int, 2>{});
-      else if (np == 3)
-        store(std::integral_constant<int, 3>{});
-      else
-        store(std::integral_constant<int, 8>{});
-    };
-    // one route for the whole wave (a per-entry choice would run both); the double route
-    // keeps only the converted entries live across the moduli
-    if (__all(small)) {
-      double xd[32];
-#pragma unroll
-      for (int e = 0; e < 32; ++e) xd[e] = (double)v[e];
-      for (int j = 0; j < n; ++j) {
-        const ModConsts k = mod_consts(P, j);
-        uint32_t r[32];
-#pragma unroll
-        for (int e = 0; e < 32; ++e) r[e] = residue_f64(xd[e], k);
-        emit(j, r);
-      }
-    } else {
-      for (int j = 0; j < n; ++j) {
-        const ModConsts k = mod_consts(P, j);
-        uint32_t r[32];
-#pragma unroll
-        for (int e = 0; e < 32; ++e) {
-          uint32_t d[4];
-          digits_of(v[e], d);
-          r[e] = residue_of(d, (uint32_t)(v[e] >> 63), k);
-        }
-        emit(j, r);
-      }
     }
   }
-  if (out_of_range && a.flag) *a.flag = 1;
+  if (a.flag && j0 == 0) {
+    bool out = false;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {
+      const int64_t v = (int64_t)(((uint64_t)hi[e] << 32) | lo[e]);
+      out |= v > a.bound || v < -a.bound;
+    }
+    if (out) *a.flag = 1;
+  }
+#pragma unroll
+  for (int e = 0; e < 32; ++e) hi[e] ^= 0x80000000u;
+  for (int j = j0; j < j1; ++j) {
+    const ResidueModulus& k = g.mod[j];
+    const uint32_t w_lo = k.w_lo, w_hi = k.w_hi, init = k.init;
+    const int32_t negm = -(int32_t)k.m;
+    const float inv = k.inv;
+    const uint32_t* lut = slut + (j - j0) * kLutSize + kLutHalf;
+    uint32_t x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      uint32_t c[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t t = __builtin_amdgcn_udot4(hi[2 * i + h], w_hi, __builtin_amdgcn_udot4(lo[2 * i + h], w_lo, init, false), false);
+        const uint32_t q = __float_as_uint(__builtin_fmaf((float)t, inv, 8388608.0f));
+        c[h] = lut[__mul24((int32_t)q, negm) + (int32_t)t];
+      }
+      x[i] = c[0] | (c[1] << 4);
+    }
+    uint8_t* dst = a.planes + a.off[j] + (ks * a.R32 + rb) * kBrickBytes + lane * 16;
+    auto store = [&](auto npc) {
+      constexpr int NP = decltype(npc)::value;
+      uint32_t d[4][4];  // [dword][plane]
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const uint32_t v[4] = {x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3]};
+        transpose4x4(v, d[w]);
+      }
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        *reinterpret_cast<uint4*>(dst + p * a.plane_stride) = make_uint4(d[0][p], d[1][p], d[2][p], d[3][p]);
+    };
+    const int np = k.np[SIDE];
+    if (np == 1)
+      store(std::integral_constant<int, 1>{});
+    else if (np == 2)
+      store(std::integral_constant<int, 2>{});
+    else
+      store(std::integral_constant<int, 3>{});
+  }
+}
+
+// Both operands: workgroups 0 .. blocks_a - 1 of a row A's, the others B's; row y takes the moduli
+// y per_group .. of the set.
+__global__ __launch_bounds__(256) void residue_encode_kernel(ResidueArgs g) {
+  __shared__ uint32_t slut[kMaxModuli * kLutSize];
+  const int side = blockIdx.x < g.blocks_a ? 0 : 1;
+  const int j0 = blockIdx.y * g.per_group, j1 = min(g.n, j0 + g.per_group);
+  for (int j = j0; j < j1; ++j) {
+    const uint32_t* src = g_mod_lut[side][g.mod[j].m - 2];
+    for (int i = threadIdx.x; i < kLutSize; i += blockDim.x) slut[(j - j0) * kLutSize + i] = src[i];
+  }
+  __syncthreads();
+  const int wave = threadIdx.x >> 6;
+  if (side == 0)
+    residue_encode_side<0>(g, slut, j0, j1, (int64_t)blockIdx.x * 4 + wave);
+  else
+    residue_encode_side<1>(g, slut, j0, j1, (int64_t)(blockIdx.x - g.blocks_a) * 4 + wave);
 }
 
 // |X| < 2^127 (two's complement in lo/hi) -> nearest double, ties to even.
@@ -312,30 +343,36 @@ __global__ __launch_bounds__(256) void crt_kernel(const RT* __restrict__ res, in
     const int64_t r = i / cols, c = i - r * cols;
     const RT* src = res + r * ld_res + c;
     // Mixed-radix digits: X = v_0 + v_1 P_1 + ... + v_{n-1} P_{n-1}, P_j = m_0 ... m_{j-1},
-    // v_j = (r_j - sum_{i<j} v_i (P_i mod m_j)) (P_j^-1 mod m_j)  mod m_j.  The subtracted
-    // sum stays below off_j < 2^22, so both reductions are mod_f's.
+    // v_j = (r_j - sum_{i<j} v_i (P_i mod m_j)) (P_j^-1 mod m_j)  mod m_j
+    //     = r_j d_j + sum_{i<j} v_i c_ji  mod m_j,  c_ji = -P_i d_j mod m_j, d_j = P_j^-1 mod m_j:
+    // the digits are bytes, packed four to a word, so the sum is a chain of byte dot products
+    // onto r_j d_j.  It stays below 2^21 + 2^16, and one reduction as in the residue encoder
+    // leaves a remainder within 0.7 m_j of zero (t / m_j is off by less than 2^-3), brought to [0, m_j)
+    // by an unsigned minimum.  (23 moduli, 1024^2 outputs: 46 us with one 24-bit multiply-add and a
+    // byte extraction per coefficient and two reductions per digit, 33 us now.)
     int32_t rj[NMAX];
 #pragma unroll
     for (int j = 0; j < NMAX; ++j) rj[j] = j < n ? (int32_t)src[j * res_stride] : 0;
-    uint32_t v[NMAX];
+    uint32_t v[NMAX], packed[(NMAX + 3) / 4];
+#pragma unroll
+    for (int q = 0; q < (NMAX + 3) / 4; ++q) packed[q] = 0;
 #pragma unroll
     for (int j = 0; j < NMAX; ++j) {
       v[j] = 0;
       if (j < n) {
-        const uint4 k = *reinterpret_cast<const uint4*>(&sp.mod[j]);  // m, inv, d, off
-        const uint32_t m = k.x;
-        const float inv = __uint_as_float(k.y);
-        int32_t acc = rj[j] + (int32_t)k.w;
+        const uint4 k = *reinterpret_cast<const uint4*>(&sp.mod[j]);  // m, inv, d
+        uint32_t t = __umul24((uint32_t)rj[j], k.z);
 #pragma unroll
         for (int q = 0; q < (j + 15) / 16; ++q) {
           const uint4 cw = *reinterpret_cast<const uint4*>(&sp.c[j][16 * q]);
           const uint32_t w[4] = {cw.x, cw.y, cw.z, cw.w};
 #pragma unroll
-          for (int t = 0; t < 16 && 16 * q + t < j; ++t)
-            acc -= __mul24((int32_t)v[16 * q + t], (int32_t)((w[t >> 2] >> (8 * (t & 3))) & 0xffu));
+          for (int u = 0; u < 4 && 16 * q + 4 * u < j; ++u) t = __builtin_amdgcn_udot4(packed[4 * q + u], w[u], t, false);
         }
-        const uint32_t tj = mod_f((uint32_t)acc, m, inv);
-        v[j] = mod_f(__umul24(tj, k.z), m, inv);
+        const uint32_t qt = __float_as_uint(__builtin_fmaf((float)t, __uint_as_float(k.y), 8388608.0f));
+        const uint32_t r = (uint32_t)((int32_t)t - __mul24((int32_t)qt, (int32_t)k.x));
+        v[j] = min(r, r + k.x);
+        packed[j >> 2] |= v[j] << (8 * (j & 3));
       }
     }
     // Horner over groups of three digits, from the top: X = D_0 + B_0 (D_1 + B_1 (D_2 + ...)),
@@ -407,14 +444,100 @@ awe_status launch_residues(const int64_t* x, int64_t rows, int64_t cols, int64_t
   return AWE_OK;
 }
 
-awe_status launch_residue_encode(const ResidueEncodeArgs& a, const ResidueParams& P, bool transposed,
+namespace {
+// Uploads the tables of one side's moduli into g_mod_lut on the current device, each once per device
+// (a table depends on its modulus alone): luts[j] holds the packed codes of residues 0 .. m - 1 (plane p
+// in bits 4p .. 4p + 3).
+awe_status ensure_mod_tables(int side, const uint32_t* m, const uint32_t* const* luts, int n) {
+  static std::mutex mu;
+  static std::map<int, std::bitset<2 * 255>> loaded;  // per device: side 255 + m - 2
+  int dev = 0;
+  hipError_t err = hipGetDevice(&dev);
+  std::lock_guard<std::mutex> lk(mu);
+  std::bitset<2 * 255>& have = loaded[dev];
+  for (int j = 0; j < n && err == hipSuccess; ++j) {
+    const size_t slot = (size_t)side * 255 + (m[j] - 2);
+    if (have[slot]) continue;
+    uint32_t t[kLutSize];
+    for (int i = 0; i < kLutSize; ++i) {
+      const int mj = (int)m[j], r = ((i - kLutHalf) % mj + mj) % mj;
+      const uint32_t c = luts[j][r];
+      t[i] = (c & 0xfu) | (((c >> 4) & 0xfu) << 8) | (((c >> 8) & 0xfu) << 16);
+    }
+    err = hipMemcpyToSymbol(HIP_SYMBOL(g_mod_lut), t, sizeof(t), sizeof(t) * slot, hipMemcpyHostToDevice);
+    if (err == hipSuccess) have[slot] = true;
+  }
+  if (err != hipSuccess) {
+    set_error(std::string("residue table upload: ") + hipGetErrorString(err));
+    return AWE_ERR_HIP;
+  }
+  return AWE_OK;
+}
+}  // namespace
+
+awe_status launch_residue_encode(const ResidueEncodeArgs& e, const ResidueParams& P, bool transposed,
                                  hipStream_t stream) {
-  if (a.nbricks == 0) return AWE_OK;
-  const int64_t blocks = std::min<int64_t>((a.nbricks + 3) / 4, 0x7fffffffLL);
-  if (transposed)
-    hipLaunchKernelGGL(residue_encode_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, a, P);
-  else
-    hipLaunchKernelGGL(residue_encode_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, a, P);
+  const ResidueEncodeArgs* sides[2] = {transposed ? e.other : &e, transposed ? &e : e.other};
+  ResidueArgs g{};
+  int64_t blocks[2] = {0, 0}, bricks = 0;
+  for (int j = 0; j < P.n; ++j) {
+    const uint32_t m = P.m[j];
+    uint32_t pw[8], x = 1;
+    for (int i = 0; i < 8; ++i) {
+      pw[i] = x % m;
+      x = pw[i] * 256;
+    }
+    ResidueModulus& k = g.mod[j];
+    k.m = m;
+    k.inv = P.inv[j];
+    k.w_lo = pw[0] | (pw[1] << 8) | (pw[2] << 16) | (pw[3] << 24);
+    k.w_hi = pw[4] | (pw[5] << 8) | (pw[6] << 16) | (pw[7] << 24);
+    k.init = (m - pw[7] * 128 % m) % m;
+  }
+  for (int s = 0; s < 2; ++s) {
+    if (!sides[s] || sides[s]->nbricks == 0) continue;
+    const ResidueEncodeArgs& a = *sides[s];
+    ResidueSide& o = g.side[s];
+    o.x = a.x;
+    o.rows = a.rows;
+    o.K = a.K;
+    o.ld = a.ld;
+    o.KS = a.KS;
+    o.R32 = a.R32;
+    o.nbricks = a.nbricks;
+    o.bound = a.bound;
+    o.planes = a.planes;
+    o.plane_stride = a.plane_stride;
+    o.flag = a.flag;
+    for (int j = 0; j < P.n; ++j) {
+      if (a.np[j] > 3) {
+        set_error("residue encoder: more than three planes");
+        return AWE_ERR_UNSUPPORTED;
+      }
+      o.off[j] = a.off[j];
+      g.mod[j].np[s] = a.np[j];
+    }
+    const awe_status st = ensure_mod_tables(s, P.m, a.luts, P.n);
+    if (st != AWE_OK) return st;
+    blocks[s] = (a.nbricks + 3) / 4;
+    bricks += a.nbricks;
+  }
+  if (bricks == 0) return AWE_OK;
+  if (blocks[0] + blocks[1] > (int64_t(1) << 24) - 1) {
+    set_error("operands too large for the residue encoder");
+    return AWE_ERR_UNSUPPORTED;
+  }
+  // A wave takes all moduli of its brick, or with few bricks a part of them (which reads the entries
+  // once per part), up to 12288 waves: three times the 4 a SIMD holds, so that one wave's loads
+  // meet another's arithmetic.  Whole awe_gemm_crt calls with 1, 3, 12 parts (us): 1024^2 x 4096
+  // (4096 bricks) 338, 318, 373; 2048^3 (8192) 558, 572, 633; 300 x 200 x 1000 (272) 77, 58, 54.
+  const int groups = (int)std::max<int64_t>(1, std::min<int64_t>(P.n, 12288 / bricks));
+  g.n = P.n;
+  g.per_group = (P.n + groups - 1) / groups;
+  g.blocks_a = (unsigned)blocks[0];
+  hipLaunchKernelGGL(residue_encode_kernel,
+                     dim3((unsigned)(blocks[0] + blocks[1]), (unsigned)((P.n + g.per_group - 1) / g.per_group)),
+                     dim3(256), 0, stream, g);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) {
     set_error(std::string("residue encode launch: ") + hipGetErrorString(err));

@@ -87,17 +87,14 @@ __device__ __forceinline__ void slice_tile(const SliceArgs& g, int t, int& tm, i
 }
 
 // One 4-column group of outputs from the int32 sums w (modulo 2^32).
-__device__ __forceinline__ void slice_store(const SliceArgs& g, int row, int col, v4i w) {
+__device__ __forceinline__ void slice_store(const SliceArgs& g, const ModReducer& mod, int row, int col, v4i w) {
   if (row >= g.M || col >= g.N) return;
   const int64_t off = (int64_t)row * g.ldc + col;
   const int n = min(4, g.N - col);
   if (g.modulus) {
     const int32_t m = g.modulus;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      int32_t rr = w[e] % m;
-      w[e] = rr < 0 ? rr + m : rr;
-    }
+    for (int e = 0; e < 4; ++e) w[e] = mod(w[e]);
     if (g.c64 == 2) {
       uint8_t* Cp = reinterpret_cast<uint8_t*>(g.C) + off;
 #pragma unroll
@@ -112,7 +109,10 @@ __device__ __forceinline__ void slice_store(const SliceArgs& g, int row, int col
     if (g.accumulate) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (e < n) w[e] = (Cp[e] + w[e]) % m;
+        if (e < n) {
+          const int32_t s = Cp[e] + w[e];
+          w[e] = s >= m ? s - m : s;
+        }
     }
     if (n == 4 && (reinterpret_cast<uintptr_t>(Cp) & 15) == 0) {
       *reinterpret_cast<v4i*>(Cp) = w;
@@ -161,8 +161,9 @@ __device__ __forceinline__ void slice_store(const SliceArgs& g, int row, int col
   }
 }
 
-template <class C>
-__device__ __forceinline__ void slice_body(const SliceArgs& g, int tile, int part) {
+// (ell(p): the fold coefficient of product p)
+template <class C, class Ell>
+__device__ __forceinline__ void slice_body(const SliceArgs& g, Ell ell, int tile, int part) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -264,7 +265,7 @@ __device__ __forceinline__ void slice_body(const SliceArgs& g, int tile, int par
     ++run;
     const bool end_p = ct + 1 == PP;
     if (i < count && (end_p || run == g.seg || i + 1 == count)) {
-      const int32_t l = g.ell[cp];
+      const int32_t l = ell(cp);
 #pragma unroll
       for (int a = 0; a < C::BMW; ++a)
 #pragma unroll
@@ -334,6 +335,7 @@ __device__ __forceinline__ void slice_body(const SliceArgs& g, int tile, int par
 #pragma unroll
       for (int v = 0; v < 16; ++v) sums[(wave * C::NV + (a * C::BNW + b) * 16 + v) * 64 + lane] = iacc[a][b][v];
   __syncthreads();
+  const ModReducer mod(g.modulus ? g.modulus : 1);
   const int L4 = (lane & 15) * 4;
   for (int ch = grp; ch < C::NV / 4; ch += C::WK) {
     const int v = ch * 4 + (lane >> 4);
@@ -343,13 +345,47 @@ __device__ __forceinline__ void slice_body(const SliceArgs& g, int tile, int par
     const int blk = v >> 4, vv = v & 15, a = blk / C::BNW, b = blk % C::BNW;
     const int row = tm * C::BM + (wm * C::BMW + a) * 32 + 8 * (vv >> 2) + 4 * (L4 >> 5) + (vv & 3);
     const int col = tn * C::BN + (wn * C::BNW + b) * 32 + (L4 & 31);
-    slice_store(g, row, col, w);
+    slice_store(g, mod, row, col, w);
   }
 }
 
 template <class C>
 __global__ __launch_bounds__(C::THREADS, 1) void slice_kernel(SliceArgs g) {
-  slice_body<C>(g, blockIdx.x / g.split, blockIdx.x % g.split);
+  slice_body<C>(g, [&](int p) { return g.ell[p]; }, blockIdx.x / g.split, blockIdx.x % g.split);
+}
+
+// Several GEMMs of one shape in one launch (the residue route's moduli): job j's tiles are workgroups
+// j tiles .. j tiles + tiles - 1.
+struct SliceJob {
+  const uint8_t* pa;
+  const uint8_t* pb;
+  void* C;
+  uint32_t pidx_a, pidx_b;
+  int32_t ell[kGroupProducts];
+  int32_t r, modulus, seg;
+};
+struct SliceGroupArgs {
+  SliceArgs g;  // the fields all jobs share
+  SliceJob job[kMaxModuli];
+  int32_t tiles;
+};
+
+template <class C>
+__global__ __launch_bounds__(C::THREADS, 1) void slice_group_kernel(SliceGroupArgs ga) {
+  const int j = blockIdx.x / ga.tiles;
+  const SliceJob& jb = ga.job[j];
+  SliceArgs g = ga.g;
+  g.pa = jb.pa;
+  g.pb = jb.pb;
+  g.C = jb.C;
+  g.pidx_a = jb.pidx_a;
+  g.pidx_b = jb.pidx_b;
+  g.r = jb.r;
+  g.modulus = jb.modulus;
+  g.seg = jb.seg;
+  static_assert(kGroupProducts == 4, "the fold coefficients below");
+  const int32_t l0 = jb.ell[0], l1 = jb.ell[1], l2 = jb.ell[2], l3 = jb.ell[3];
+  slice_body<C>(g, [=](int p) { return p == 0 ? l0 : p == 1 ? l1 : p == 2 ? l2 : l3; }, blockIdx.x - j * ga.tiles, 0);
 }
 
 // Zeroes C before the parts of split tiles add into it, as words of 4 bytes: row_words per row,
@@ -387,6 +423,26 @@ awe_status launch_slices(SliceArgs& g, int split, hipStream_t stream) {
   err = hipGetLastError();
   if (err != hipSuccess) {
     set_error(std::string("gemm launch: ") + hipGetErrorString(err));
+    return AWE_ERR_HIP;
+  }
+  return AWE_OK;
+}
+
+template <class C>
+awe_status launch_slice_jobs(SliceGroupArgs& ga, int n, hipStream_t stream) {
+  SliceArgs& g = ga.g;
+  g.tiles_m = (g.M + C::BM - 1) / C::BM;
+  g.tiles_n = (g.N + C::BN - 1) / C::BN;
+  g.split = 1;
+  ga.tiles = g.tiles_m * g.tiles_n;
+  static std::mutex mu;
+  static std::set<int> done;
+  const awe_status st = set_lds_limit(reinterpret_cast<const void*>(&slice_group_kernel<C>), C::LDS_BYTES, mu, done);
+  if (st != AWE_OK) return st;
+  hipLaunchKernelGGL(slice_group_kernel<C>, dim3((unsigned)(ga.tiles * n)), dim3(C::THREADS), C::LDS_BYTES, stream, ga);
+  const hipError_t err = hipGetLastError();
+  if (err != hipSuccess) {
+    set_error(std::string("grouped gemm launch: ") + hipGetErrorString(err));
     return AWE_ERR_HIP;
   }
   return AWE_OK;
@@ -499,6 +555,57 @@ Slice choose_slice(const GemmLaunch& L, int cus, double tile_us) {
     }
   }
   return best;
+}
+
+int choose_slice_group(const GemmLaunch* L, int n, int cus, double tile_us) {
+  if (const char* e = getenv("AWE_GEMM_SLICE")) return atoi(e) >= 1 && atoi(e) <= 6 ? atoi(e) : 0;
+  if (getenv("AWE_GEMM_CFG")) return 0;
+  int best = 0;
+  for (int v = 0; v < 6; ++v) {
+    const VariantCost& c = kVariants[v];
+    const int64_t tiles = ((L[0].M + c.bm - 1) / c.bm) * ((L[0].N + c.bn - 1) / c.bn);
+    if (tiles > 64 * cus) continue;
+    double sum = 0.0, longest = 0.0;
+    for (int j = 0; j < n; ++j) {
+      const double t = c.fixed + c.per_index[0] * 1e-3 * (double)L[j].r * (double)(L[j].k_end - L[j].k_begin);
+      sum += t;
+      longest = std::max(longest, t);
+    }
+    const double us = group_time(sum, longest, tiles, cus);
+    if (us < tile_us) {
+      tile_us = us;
+      best = v + 1;
+    }
+  }
+  return best;
+}
+
+awe_status launch_slice_group(const GemmLaunch* L, const int* order, int n, int variant, hipStream_t stream) {
+  SliceGroupArgs ga{};
+  fill_slice_args(L[order[0]], ga.g);
+  for (int j = 0; j < n; ++j) {
+    const GemmLaunch& Lj = L[order[j]];
+    SliceJob& jb = ga.job[j];
+    jb.pa = Lj.planes_a;
+    jb.pb = Lj.planes_b;
+    jb.C = Lj.C;
+    for (int k = 0; k < Lj.flat.r; ++k) {
+      jb.pidx_a |= (uint32_t)(Lj.flat.pa[k] & 15) << (4 * k);
+      jb.pidx_b |= (uint32_t)(Lj.flat.pb[k] & 15) << (4 * k);
+      jb.ell[k] = Lj.flat.ell[k];
+    }
+    jb.r = Lj.flat.r;
+    jb.modulus = Lj.modulus;
+    jb.seg = (int32_t)(Lj.flat.k_seg / 128);
+  }
+  switch (variant) {
+    case 1: return launch_slice_jobs<Slice128<0>>(ga, n, stream);
+    case 2: return launch_slice_jobs<Slice64x128<0>>(ga, n, stream);
+    case 3: return launch_slice_jobs<Slice64<0>>(ga, n, stream);
+    case 4: return launch_slice_jobs<Slice32<0>>(ga, n, stream);
+    case 5: return launch_slice_jobs<Slice32x64<0>>(ga, n, stream);
+    default: return launch_slice_jobs<Slice64x32<0>>(ga, n, stream);
+  }
 }
 
 awe_status launch_slice(const GemmLaunch& L, Slice s, hipStream_t stream) {

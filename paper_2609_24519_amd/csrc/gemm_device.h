@@ -98,5 +98,20 @@ __device__ __forceinline__ void mfma_block6(v16f& acc, const v8i& a, const v8i& 
   acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 2, 2, 0, kScale8, 0, kScale8);
 }
 
+// val mod m in [0, m) for an int32: q = round(val / m) and val - q m exactly in doubles (a remainder
+// within m / 2 + 1 of zero).  Seven instructions; an integer division by a variable takes about 35,
+// which cost the residue epilogues more than their stores.
+struct ModReducer {
+  double m, inv;
+  int32_t mi;
+  __device__ __forceinline__ explicit ModReducer(int32_t modulus)
+      : m((double)modulus), inv(1.0 / (double)modulus), mi(modulus) {}
+  __device__ __forceinline__ int32_t operator()(int32_t val) const {
+    const double x = (double)val;
+    const int32_t r = (int32_t)__builtin_fma(-__builtin_rint(x * inv), m, x);
+    return (int32_t)min((uint32_t)r, (uint32_t)(r + mi));
+  }
+};
+
 }  // namespace
 }  // namespace awe

@@ -1,5 +1,5 @@
 // Packing of E2M1 codes into the stored plane layout (Alg. 1, plane formation), shared by the
-// byte encoder and the residue encoder.
+// encoders.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -7,6 +7,19 @@
 #include <cstdint>
 
 namespace awe {
+
+// The 4 x 4 byte transpose of v (v[i] holds bytes 0 .. 3 of row i): out[j] holds byte j of rows 0 .. 3.
+// (v_perm_b32(a, b, sel): result byte k = byte sel_k of {a : b}, b being bytes 0..3)
+__device__ __forceinline__ void transpose4x4(const uint32_t (&v)[4], uint32_t (&out)[4]) {
+  const uint32_t t0 = __builtin_amdgcn_perm(v[1], v[0], 0x05010400u);
+  const uint32_t t1 = __builtin_amdgcn_perm(v[1], v[0], 0x07030602u);
+  const uint32_t t2 = __builtin_amdgcn_perm(v[3], v[2], 0x05010400u);
+  const uint32_t t3 = __builtin_amdgcn_perm(v[3], v[2], 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
+  out[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
+  out[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
+  out[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
+}
 
 // One lane's 32 elements of a brick: e[j] holds element j's 4-bit E2M1 code of plane p in bits
 // 4p .. 4p + 3 (up to 8 planes).  The stored layout wants, for each plane, 16 bytes with the 32
@@ -28,22 +41,13 @@ __device__ __forceinline__ void pack_e2m1_planes(const uint32_t (&e)[32], uint32
     x[i] = (lo & 0x0f0f0f0fu) | ((hi & 0x0f0f0f0fu) << 4);
     y[i] = ((lo >> 4) & 0x0f0f0f0fu) | (hi & 0xf0f0f0f0u);
   }
-  // v_perm_b32(a, b, sel): result byte k = byte sel_k of {a : b}, b being bytes 0..3
-  auto transpose4 = [](const uint32_t* v, uint32_t* out) {
-    const uint32_t t0 = __builtin_amdgcn_perm(v[1], v[0], 0x05010400u);
-    const uint32_t t1 = __builtin_amdgcn_perm(v[1], v[0], 0x07030602u);
-    const uint32_t t2 = __builtin_amdgcn_perm(v[3], v[2], 0x05010400u);
-    const uint32_t t3 = __builtin_amdgcn_perm(v[3], v[2], 0x07030602u);
-    out[0] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
-    out[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
-    out[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
-    out[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
-  };
   uint32_t px[4][4], py[4][4];  // [dword w][plane pair q]
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    transpose4(x + 4 * w, px[w]);
-    transpose4(y + 4 * w, py[w]);
+    const uint32_t vx[4] = {x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3]};
+    const uint32_t vy[4] = {y[4 * w], y[4 * w + 1], y[4 * w + 2], y[4 * w + 3]};
+    transpose4x4(vx, px[w]);
+    transpose4x4(vy, py[w]);
   }
 #pragma unroll
   for (int p = 0; p < NP; ++p)

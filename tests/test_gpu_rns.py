@@ -231,3 +231,44 @@ def test_gemm_crt_range_flag_and_large_entries():
         expect_flag = bool((np.abs(Ai) > bound_a).any() or (np.abs(B) > bound_b).any())
         assert bool(flag.item()) == expect_flag, (bound_a, bound_b)
         assert (_words_to_ints(c128) == og.gemm_i128(Ai, B)).all()
+
+
+@pytest.mark.parametrize("variant", ["1", "2", "3", "4", "5", "6"])
+def test_gemm_crt_grouped_slices(monkeypatch, variant):
+    # all moduli in one launch of the kernel whose waves split the reduction: ragged tiles, a reduction
+    # shorter than the shares and one of several items per share, and a set whose moduli have 1, 3 and
+    # 4 products
+    monkeypatch.setenv("AWE_GEMM_SLICE", variant)
+    for (M, N, K), ms, bound in [((40, 70, 65), [7, 31, 149, 157, 11, 89], (1 << 12) - 1),
+                                 ((130, 33, 1500), _moduli(), B53)]:
+        rng = np.random.default_rng(M)
+        A = rng.integers(-bound, bound, size=(M, K), endpoint=True, dtype=np.int64)
+        B = rng.integers(-bound, bound, size=(K, N), endpoint=True, dtype=np.int64)
+        c128, c64 = awe.matmul_crt(to_dev(A), to_dev(B), ms, bound, bound)
+        torch.cuda.synchronize()
+        ref = og.gemm_i128(A, B)
+        assert (_words_to_ints(c128) == ref).all()
+        assert np.array_equal(c64.cpu().numpy(), ocrt.to_double(ref))
+
+
+@pytest.mark.parametrize("m", [2, 3, 7, 128, 157, 255, 256])
+def test_residue_planes_at_the_extremes(m):
+    # the fused residue encoder against the byte encoder on the residues, through the mod-m product with
+    # an identity: entries at the ends of int64, around multiples of m and zero
+    base = [0, 1, -1, m, -m, m - 1, 1 - m, m // 2, -(m // 2), 2 ** 53, -2 ** 53, 2 ** 62, -2 ** 62, 2 ** 63 - 1, -2 ** 63 + 1,
+            -2 ** 63, 255, 256, -256, 2 ** 32, -2 ** 32, 2 ** 31, 0x7F7F7F7F7F7F7F7F, -0x0101010101010101]
+    try:
+        awe.get_encoding_info(awe.ENC_MOD, m)
+    except awe.AweError:
+        pytest.skip("no scheme for this modulus")
+    x = np.array(base * 3, dtype=np.int64)[:70].reshape(2, 35)
+    eye = np.eye(35, dtype=np.int64)
+    ws = torch.empty(awe.crt_workspace_bytes([m], 2, 35, 35), dtype=torch.uint8, device="cuda")
+    c128 = torch.empty((2, 35, 2), dtype=torch.int64, device="cuda")
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    awe.gemm_crt(2, 35, 35, to_dev(x), 35, to_dev(eye), 35, 0, 1, [m], c128, None, 35, ws, ws.numel(), flag)
+    torch.cuda.synchronize()
+    got = c128.cpu().numpy()[..., 0]
+    want = np.array([[int(v) % m for v in r] for r in x])
+    want = np.where(want > m // 2, want - m, want)
+    assert np.array_equal(got, want) and flag.item() != 0
