@@ -133,10 +133,25 @@ def _ptr(x):
     return x.data_ptr()
 
 
+_torch_c = None  # torch._C once CUDA is initialised
+
+
+def _current_stream():
+    """Handle of torch's current stream on the current device.  Without the Stream object that
+    torch.cuda.current_stream() builds on every call (2.8 us, a quarter of a small product's host time)."""
+    global _torch_c
+    if _torch_c is None:
+        import torch
+        handle = torch.cuda.current_stream().cuda_stream  # initialises CUDA
+        if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+            _torch_c = torch._C
+        return handle
+    return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
