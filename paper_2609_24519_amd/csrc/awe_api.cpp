@@ -71,7 +71,7 @@ int64_t launch_k_limit(const Scheme& s) {
 // ell_d[i + j] receives it.  AWE_GEMM_ALLPAIRS=0 keeps such schemes on the product-major
 // stream (for comparison).
 bool all_pairs_by_sum(const Scheme& s, int64_t* ell_d) {
-  const char* e = getenv("AWE_GEMM_ALLPAIRS");
+  const char* e = tuning("AWE_GEMM_ALLPAIRS");
   if (e && atoi(e) == 0) return false;
   if (s.n_lgroups != 1 || s.na != 3 || s.nb != 3 || s.r != 9 || s.scale_weights || s.wide) return false;
   for (int k = 0; k < 3; ++k)
@@ -98,7 +98,7 @@ bool all_pairs_by_sum(const Scheme& s, int64_t* ell_d) {
 // side, and its four pairs add into three accumulator groups, one per k + l.  AWE_GEMM_ALLPAIRS=0
 // keeps it on one launch per group.
 bool pairs_of_halves(const Scheme& s, int64_t* inner, int64_t* outer) {
-  const char* e = getenv("AWE_GEMM_ALLPAIRS");
+  const char* e = tuning("AWE_GEMM_ALLPAIRS");
   if (e && atoi(e) == 0) return false;
   if (s.n_lgroups != 3 || s.na != 6 || s.nb != 6 || s.r != 12 || s.scale_weights || s.modulus) return false;
   for (int k = 0; k < 6; ++k)
@@ -147,6 +147,7 @@ FlatProducts flat_products(const Scheme& s, int g, int first_a, int first_b, int
 awe_status plan_gemm(const Scheme& s, int64_t M, int64_t N, int64_t K, const void* pa, const void* pb,
                      void* C, int64_t ldc, awe_dtype c_type, int64_t k_seg, std::vector<GemmLaunch>* plan) {
   plan->clear();
+  read_tuning();
   if (M < 0 || N < 0 || K < 0) return fail(AWE_ERR_INVALID_VALUE, "negative size");
   if (c_type != AWE_I32 && c_type != AWE_I64) return fail(AWE_ERR_INVALID_VALUE, "bad c_type");
   if (s.modulus && c_type != AWE_I32) return fail(AWE_ERR_INVALID_VALUE, "residues are written as int32");
@@ -339,18 +340,20 @@ awe_status exact_impl(const Scheme& s, int64_t M, int64_t N, int64_t K, const vo
     return fail(AWE_ERR_WORKSPACE, "workspace smaller than awe_workspace_bytes");
   uint8_t* pa = reinterpret_cast<uint8_t*>(ws);
   uint8_t* pb = pa + ba;
-  awe_status st = AWE_OK;
+  std::vector<GemmLaunch> plan;
+  awe_status st = plan_gemm(s, M, N, K, pa, pb, C, ldc, c_type, 0, &plan);
+  if (st != AWE_OK) return st;
+  EncodeLaunch ea, eb;
   if (K > 0) {
-    EncodeLaunch ea, eb;
     st = plan_encode(s, AWE_SIDE_A, A, M, K, lda, pa, flag, &ea);
     if (st != AWE_OK) return st;
     st = plan_encode(s, AWE_SIDE_B, B, N, K, ldb, pb, flag, &eb);
     if (st != AWE_OK) return st;
-    ea.other = &eb;  // one launch for both
-    st = launch_encode(ea, stream);
-    if (st != AWE_OK) return st;
+    ea.other = &eb;  // one launch for both, with the first of the plan
+    plan[0].operands = &ea;
   }
-  return gemm_planes_impl(s, M, N, K, pa, pb, C, ldc, c_type, 0, stream);
+  for (size_t i = 0; st == AWE_OK && i < plan.size(); ++i) st = launch_gemm(plan[i], stream);
+  return st;
 }
 
 // ---- residue number system ----
@@ -724,7 +727,8 @@ awe_status awe_gemm_crt(int64_t M, int64_t N, int64_t K, const int64_t* A, int64
     single = single && plan.size() == 1;
     all.insert(all.end(), plan.begin(), plan.end());
   }
-  const char* ge = getenv("AWE_GEMM_GROUPED");
+  read_tuning();
+  const char* ge = tuning("AWE_GEMM_GROUPED");
   if (single && !(ge && atoi(ge) == 0) && gemm_group_ok(all.data(), (int)all.size())) {
     st = launch_gemm_group(all.data(), (int)all.size(), stream);
     if (st != AWE_OK) return st;

@@ -2,10 +2,14 @@
 #pragma once
 #include <array>
 #include <cstdint>
+#include <cstdlib>
+#include <cstring>
 #include <mutex>
 #include <set>
 #include <string>
 #include <vector>
+
+#include <unistd.h>
 
 #include "../../include/awe.h"
 
@@ -14,6 +18,16 @@ namespace awe {
 constexpr int kMaxLimbs = AWE_MAX_LIMBS;
 constexpr int kMaxPlanes = AWE_MAX_PLANES;
 constexpr int kMaxProducts = AWE_MAX_PRODUCTS;
+
+// Environment variables AWE_GEMM_* (they change launches, never results).  A launch consults some
+// twenty of them, so it first looks once whether any is set (read_tuning) and asks for single ones
+// (tuning) only then: 1.3 us of a call's host time otherwise.
+inline thread_local bool t_tuned = false;
+inline void read_tuning() {
+  t_tuned = false;
+  for (char** e = environ; e && *e && !t_tuned; ++e) t_tuned = std::strncmp(*e, "AWE_GEMM_", 9) == 0;
+}
+inline const char* tuning(const char* name) { return t_tuned ? std::getenv(name) : nullptr; }
 
 // Plane layout constants (the MFMA fragment "brick", see include/awe.h).
 constexpr int kBrickRows = 32;     // rows (A) or columns (B) per brick
@@ -191,6 +205,9 @@ struct GemmLaunch {
   int log2D;
   int32_t modulus;
   FlatProducts flat;
+  // Both operands, to be encoded into the planes before the products (their launch, nullable: the
+  // planes are there already).  The launcher may multiply straight from them instead.
+  const EncodeLaunch* operands;
 };
 awe_status launch_gemm(const GemmLaunch& g, hipStream_t stream);
 
@@ -209,7 +226,10 @@ struct Slice {
 // The variant that suits a launch, if it beats the tile configurations' `tile_us` on `cus` CUs.
 Slice choose_slice(const GemmLaunch& L, int cus, double tile_us);
 awe_status launch_slice(const GemmLaunch& L, Slice s, hipStream_t stream);
-// The same for launches that share one (launch_gemm_group's; order: the jobs' order).
+// Whether one kernel does the launch's whole product sooner, from the operands, and that kernel.
+bool choose_direct(const GemmLaunch& L, int cus);
+awe_status launch_direct(const GemmLaunch& L, hipStream_t stream);
+// choose_slice for launches that share one (launch_gemm_group's; order: the jobs' order).
 int choose_slice_group(const GemmLaunch* L, int n, int cus, double tile_us);
 awe_status launch_slice_group(const GemmLaunch* L, const int* order, int n, int variant, hipStream_t stream);
 // Time of a grouped launch (us): each job has `tiles` tiles, the jobs' tile times add up to `sum`, the

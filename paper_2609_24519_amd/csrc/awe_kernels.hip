@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdlib>
 #include <map>
 #include <mutex>
@@ -11,6 +12,7 @@
 #include <type_traits>
 
 #include "awe_internal.h"
+#include "encode_device.h"
 #include "gemm_device.h"
 #include "gemm_layout.h"
 #include "plane_pack.h"
@@ -28,10 +30,6 @@ static __device__ __align__(256) uint8_t scratch[kNoallocBytes];
 
 namespace {
 
-struct LutArg {
-  uint32_t v[256];
-};
-
 // ---------------------------------------------------------------------------
 // Encoder (Alg. 1, table lookup and plane formation).  One wave per 1 KiB
 // brick: lane L = 32 h + t turns the 32 inputs of row rb*32 + t at reduction
@@ -39,36 +37,12 @@ struct LutArg {
 // plane values (combinations of limbs included) come from one 256-entry table
 // of packed E2M1 codes, so forming a combination plane costs nothing here.
 // ---------------------------------------------------------------------------
-struct EncodeArgs {
-  const uint8_t* x;
-  int64_t rows, K, ld, KS, R32, nbricks;
-  int nplanes, nplanes8;
-  bool fp6;
-  uint8_t* planes;
-  int64_t plane_stride;
-  int32_t* flag;
-};
-
-// 16 and 8 bytes from any address (the memory system takes unaligned vector loads; rows of an odd
-// length were read byte by byte before: 14 us a side at 1001 x 2049 and 2049 x 1537).
-struct __attribute__((packed)) Any16 {
-  uint32_t w[4];
-};
-struct __attribute__((packed)) Any8 {
-  uint32_t w[2];
-};
-
-// B side: a wave's 64 x 32 input block lies column-major in LDS, kTileCol bytes per column (64 rows +
-// 16 bytes of padding, so that the 16-byte column reads hit distinct banks).
-constexpr int kTileCol = 80;
-
 // The bricks of one side that workgroup `block` of `blocks` produces.
 template <bool kTransposed>
 __device__ __forceinline__ void encode_side(const EncodeArgs& a, const uint32_t* slut, uint8_t* tblk, unsigned block,
                                             unsigned blocks) {
-  const uint8_t* __restrict__ x = a.x;
   uint8_t* __restrict__ planes = a.planes;
-  const int64_t rows = a.rows, K = a.K, ld = a.ld, KS = a.KS, R32 = a.R32, nbricks = a.nbricks;
+  const int64_t KS = a.KS, R32 = a.R32, nbricks = a.nbricks;
   const int64_t plane_stride = a.plane_stride;
   const int nplanes = a.nplanes, nplanes8 = a.nplanes8;
   int32_t* flag = a.flag;
@@ -93,71 +67,8 @@ __device__ __forceinline__ void encode_side(const EncodeArgs& a, const uint32_t*
     rb = brick / KS;
     ks = brick - rb * KS;
   }
-  const int64_t row = rb * kBrickRows + (lane & 31);
-  const int64_t k0 = ks * kBrickK + (lane >> 5) * 32;
-  const bool row_ok = row < rows;
-
   uint32_t e[32];
-  if (!kTransposed) {
-    const uint8_t* src = x + row * ld + k0;
-    if (row_ok && k0 + 32 <= K) {
-      const Any16 lo = *reinterpret_cast<const Any16*>(src), hi = *reinterpret_cast<const Any16*>(src + 16);
-#pragma unroll
-      for (int j = 0; j < 32; ++j) e[j] = slut[((j < 16 ? lo.w[j >> 2] : hi.w[(j - 16) >> 2]) >> (8 * (j & 3))) & 0xff];
-    } else {
-#pragma unroll
-      for (int j = 0; j < 32; ++j) e[j] = 0u;
-      if (row_ok && k0 < K) {
-#pragma unroll
-        for (int j = 0; j < 32; ++j)
-          if (k0 + j < K) e[j] = slut[src[j]];
-      }
-    }
-  } else {
-    // B side, K x N row-major: the brick needs the 64 x 32 block of B at rows
-    // (reduction indices) ks*64 .. +63 and columns rb*32 .. +31.  Lane l takes columns
-    // 8 (l & 3) .. +7 of block rows 4 (l >> 2) .. +3, transposes them in registers and writes four
-    // rows of each column as one word of this wave's column-major tile; lane 32 h + t then reads
-    // rows 32 h .. 32 h + 31 of column t as two 16-byte words.
-    uint8_t* tw = tblk + (threadIdx.x >> 6) * (32 * kTileCol);
-    const int64_t n0 = rb * kBrickRows;
-    const int c0 = 8 * (lane & 3), r0 = 4 * (lane >> 2);
-    const int64_t kr = ks * kBrickK + r0;
-    const uint8_t* src = x + kr * ld + n0 + c0;
-    uint32_t v[2][4];
-    if (n0 + 32 <= rows && kr + 4 <= K) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const Any8 t = *reinterpret_cast<const Any8*>(src + i * ld);
-        v[0][i] = t.w[0];
-        v[1][i] = t.w[1];
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[0][i] = v[1][i] = 0;
-        if (kr + i < K)
-          for (int c = 0; c < 8; ++c)
-            if (n0 + c0 + c < rows) v[c >> 2][i] |= (uint32_t)src[i * ld + c] << (8 * (c & 3));
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      uint32_t t[4];
-      transpose4x4(v[h], t);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) *reinterpret_cast<uint32_t*>(tw + (c0 + 4 * h + c) * kTileCol + r0) = t[c];
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS writes are done
-    __builtin_amdgcn_wave_barrier();
-    const uint8_t* col = tw + (lane & 31) * kTileCol + (lane >> 5) * 32;
-    const uint4 q0 = *reinterpret_cast<const uint4*>(col);
-    const uint4 q1 = *reinterpret_cast<const uint4*>(col + 16);
-    const uint32_t cw[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-#pragma unroll
-    for (int j = 0; j < 32; ++j)
-      e[j] = (row_ok && k0 + j < K) ? slut[(cw[j >> 2] >> (8 * (j & 3))) & 0xff] : 0u;
-  }
+  brick_codes<kTransposed>(a, rb, ks, slut, tblk + (threadIdx.x >> 6) * (32 * kTileCol), e);
   uint32_t bad = 0;
 #pragma unroll
   for (int j = 0; j < 32; ++j) bad |= e[j];
@@ -170,14 +81,8 @@ __device__ __forceinline__ void encode_side(const EncodeArgs& a, const uint32_t*
     uint8_t* unit = planes + ((ks >> 1) * R32 + rb) * (3 * kBrickBytes);
     const int i = (int)(ks & 1);
     for (int p = 0; p < nplanes; ++p) {
-      uint32_t d[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-      for (int j = 0; j < 32; ++j) {
-        const uint32_t c = (e[j] >> (8 * p)) & 0x3fu;
-        const int bit = 6 * j;
-        d[bit >> 5] |= c << (bit & 31);
-        if ((bit & 31) > 26) d[(bit >> 5) + 1] |= c >> (32 - (bit & 31));
-      }
+      uint32_t d[6];
+      pack_e2m3_plane(e, p, d);
       uint8_t* u = unit + p * (3 * plane_stride / 2);
       *reinterpret_cast<uint4*>(u + i * 1024 + lane * 16) = make_uint4(d[0], d[1], d[2], d[3]);
       *reinterpret_cast<uint2*>(u + 2048 + i * 512 + lane * 8) = make_uint2(d[4], d[5]);
@@ -1257,15 +1162,19 @@ __global__ void fill_zero_kernel(uint8_t* C, int64_t rows, int64_t row_bytes, in
 // Compute units of the current device (AWE_GEMM_CUS overrides the count used
 // for planning the rounds of workgroups; it changes no result).
 int compute_units() {
-  const char* e = getenv("AWE_GEMM_CUS");
+  const char* e = tuning("AWE_GEMM_CUS");
   if (e && atoi(e) > 0) return atoi(e);
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    int v = 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      cus = v;
+  static std::atomic<int> known[64];  // per device; 0: not asked yet
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  if (dev >= 0 && dev < 64) {
+    const int v = known[dev].load(std::memory_order_relaxed);
+    if (v > 0) return v;
   }
-  return cus;
+  int v = 0;
+  if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) return 256;
+  if (dev >= 0 && dev < 64) known[dev].store(v, std::memory_order_relaxed);
+  return v;
 }
 
 // Rounds of workgroups for `tiles` tiles on `cus` CUs, with the ragged last
@@ -1292,7 +1201,7 @@ struct Split {
 Split best_split(int64_t tiles, int cus, int stages, double work, double fixed, double outputs, bool allowed) {
   Split best{1, rounds(tiles, cus) * (work + fixed)};
   if (!allowed) return best;
-  const char* e = getenv("AWE_GEMM_SPLIT");
+  const char* e = tuning("AWE_GEMM_SPLIT");
   const int forced = e ? atoi(e) : 0;
   if (forced > 0) return forced <= stages ? Split{forced, best.time} : best;
   for (int s = 2; s <= 16 && tiles * s <= cus && stages >= 2 * s; ++s) {
@@ -1326,7 +1235,7 @@ struct Choice {
   double time;
 };
 Choice choose_cfg(const GemmLaunch& L) {
-  const char* e = getenv("AWE_GEMM_CFG");
+  const char* e = tuning("AWE_GEMM_CFG");
   const int forced = e ? atoi(e) : -1;
   if (e2m1_cfg(forced)) return Choice{forced, 0.0};
   const int cus = compute_units();
@@ -1352,7 +1261,7 @@ struct GroupChoice {
   double us;
 };
 GroupChoice choose_group_cfg(const GemmLaunch* L, int n) {
-  const char* e = getenv("AWE_GEMM_CFG");
+  const char* e = tuning("AWE_GEMM_CFG");
   const int forced = e ? atoi(e) : -1;
   if (forced >= 0) return GroupChoice{forced, 0.0};
   const int cus = compute_units();
@@ -1376,7 +1285,7 @@ GroupChoice choose_group_cfg(const GemmLaunch* L, int n) {
 // blocks in LDS, 6: as 5 with 2 blocks in LDS and 2 stages) overrides the default 5, the
 // fastest measured at 8192^3 (in one process: 3: 1.16-1.18 ms, 5: 1.07-1.10 ms, 6: 1.24-1.26 ms).
 int choose_cfg_e2m3() {
-  const char* e = getenv("AWE_GEMM_CFG_E2M3");
+  const char* e = tuning("AWE_GEMM_CFG_E2M3");
   const int forced = e ? atoi(e) : -1;
   return forced == 0 || forced == 1 || forced == 3 || forced == 6 ? forced : 5;
 }
@@ -1614,28 +1523,6 @@ awe_status noalloc_planes(void** out) {
 }
 
 namespace {
-// Kernel arguments and workgroups of one side (none for an empty one).
-unsigned encode_args(const EncodeLaunch& e, EncodeArgs& a) {
-  const int64_t rb = (e.rows + kBrickRows - 1) / kBrickRows;
-  a.x = reinterpret_cast<const uint8_t*>(e.x);
-  a.rows = e.rows;
-  a.K = e.K;
-  a.ld = e.ld;
-  a.KS = (e.K + kKPad - 1) / kKPad * kKPad / kBrickK;
-  a.R32 = rb;
-  // one brick per wave (the B side in groups of four column blocks, the last group padded); past
-  // 2^23 workgroups the waves walk several bricks each.  A wide encoding's workgroups stage 16 KiB
-  // of table each: past 2048 of them (8 per CU) their waves walk several bricks.
-  a.nbricks = e.transposed ? (rb + 3) / 4 * 4 * a.KS : rb * a.KS;
-  a.nplanes = e.nplanes;
-  a.nplanes8 = e.nplanes8;
-  a.fp6 = e.fp6;
-  a.planes = e.planes;
-  a.plane_stride = e.plane_stride;
-  a.flag = e.flag;
-  return (unsigned)std::min<int64_t>((a.nbricks + 3) / 4, e.wide ? 2048 : (int64_t(1) << 23));
-}
-
 awe_status encode_launched() {
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) {
@@ -1676,6 +1563,7 @@ awe_status launch_encode(const EncodeLaunch& e, hipStream_t stream) {
 }
 
 awe_status launch_gemm(const GemmLaunch& L, hipStream_t stream) {
+  read_tuning();
   if (L.M == 0 || L.N == 0) return AWE_OK;
   const int64_t esize = L.c_u8 && L.modulus ? 1 : (L.c_type == AWE_I64 ? 8 : 4);
   if (L.k_end <= L.k_begin) {
@@ -1688,6 +1576,11 @@ awe_status launch_gemm(const GemmLaunch& L, hipStream_t stream) {
       return AWE_ERR_HIP;
     }
     return AWE_OK;
+  }
+  if (L.operands) {
+    if (choose_direct(L, compute_units())) return launch_direct(L, stream);
+    const awe_status st = launch_encode(*L.operands, stream);
+    if (st != AWE_OK) return st;
   }
   // Outputs of few tiles: the kernel whose waves split the reduction, where it is sooner done than
   // the tile configuration below (only if that one is not asked for).
@@ -1719,7 +1612,7 @@ awe_status launch_gemm(const GemmLaunch& L, hipStream_t stream) {
       g.sb[k] = L.scale_b[k];
     }
     // AWE_GEMM_CFG_SHARED: 1 reads each k-step's fragments in place
-    const char* e = getenv("AWE_GEMM_CFG_SHARED");
+    const char* e = tuning("AWE_GEMM_CFG_SHARED");
     if (e && atoi(e) == 1) return launch_tile<Cfg8w64x64shp0>(g, L, stream);
     return launch_tile<Cfg8w64x64sh>(g, L, stream);
   }
@@ -1773,6 +1666,7 @@ bool gemm_group_ok(const GemmLaunch* L, int n) {
 }
 
 awe_status launch_gemm_group(const GemmLaunch* L, int n, hipStream_t stream) {
+  read_tuning();
   if (!gemm_group_ok(L, n)) {
     set_error("these GEMMs cannot share one launch");
     return AWE_ERR_UNSUPPORTED;

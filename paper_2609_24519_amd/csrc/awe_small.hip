@@ -9,6 +9,7 @@
 #include <string>
 
 #include "awe_internal.h"
+#include "encode_device.h"
 #include "gemm_device.h"
 
 namespace awe {
@@ -123,41 +124,40 @@ __device__ __forceinline__ void slice_store(const SliceArgs& g, const ModReducer
     }
     return;
   }
-  int64_t t[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) t[e] = (int64_t)(w[e] >> g.log2D) * g.outer;
   if (g.c64) {
     int64_t* Cp = reinterpret_cast<int64_t*>(g.C) + off;
-    if (g.split > 1) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (e < n) atomicAdd(reinterpret_cast<unsigned long long*>(Cp + e), (unsigned long long)t[e]);
-      return;
-    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (e < n) Cp[e] = g.accumulate ? Cp[e] + t[e] : t[e];
+      if (e < n) {
+        const int64_t t = (int64_t)(w[e] >> g.log2D) * g.outer;
+        if (g.split > 1)
+          atomicAdd(reinterpret_cast<unsigned long long*>(Cp + e), (unsigned long long)t);
+        else
+          Cp[e] = g.accumulate ? Cp[e] + t : t;
+      }
     return;
   }
+  // (int32 C takes the low word of outer (sum / D))
   int32_t* Cp = reinterpret_cast<int32_t*>(g.C) + off;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) w[e] = (int32_t)((uint32_t)(w[e] >> g.log2D) * (uint32_t)g.outer);
   if (g.split > 1) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (e < n) atomicAdd(Cp + e, (int32_t)t[e]);
+      if (e < n) atomicAdd(Cp + e, w[e]);
     return;
   }
-  v4i o = {(int32_t)t[0], (int32_t)t[1], (int32_t)t[2], (int32_t)t[3]};
   if (g.accumulate) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (e < n) o[e] = (int32_t)((uint32_t)o[e] + (uint32_t)Cp[e]);
+      if (e < n) w[e] = (int32_t)((uint32_t)w[e] + (uint32_t)Cp[e]);
   }
   if (n == 4 && (reinterpret_cast<uintptr_t>(Cp) & 15) == 0) {
-    *reinterpret_cast<v4i*>(Cp) = o;
+    __builtin_nontemporal_store(w, reinterpret_cast<v4i*>(Cp));
   } else {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (e < n) Cp[e] = o[e];
+      if (e < n) Cp[e] = w[e];
   }
 }
 
@@ -282,10 +282,10 @@ __device__ __forceinline__ void slice_body(const SliceArgs& g, Ell ell, int tile
   };
 
   // Item i sits in buffer i % NST and its fragments are in registers when its MFMAs begin.  Between
-  // these MFMAs the next item's fragments are read and the copies of item i + NST are issued into
-  // item i's buffer, spread so that neither queues up.  Then the wave waits until item i + 2 has
-  // landed and its reads are done; where waves share copies, a barrier makes that true of all of
-  // them.
+  // the first 3/4 of these MFMAs the next item's fragments are read and the copies of item i + NST
+  // are issued into item i's buffer, spread so that neither queues up.  Then the wave waits until item
+  // i + 2 has landed and its reads are done; where waves share copies, a barrier makes that true of
+  // all of them, and the last quarter of the MFMAs covers it.
 #pragma unroll
   for (int s = 0; s < C::NST; ++s) {
     static_for<0, C::PER>([&](auto cc) { copy_one(cc, s); });
@@ -301,18 +301,23 @@ __device__ __forceinline__ void slice_body(const SliceArgs& g, Ell ell, int tile
   int buf = 0;
   auto stage = [&](const Frags& cur, Frags& nxt, int i) {
     const int nbuf = buf + 1 == C::NST ? 0 : buf + 1;
+    constexpr int BAR = 2 * NM * 3 / 4 > 0 ? 2 * NM * 3 / 4 : 1;  // MFMAs before the wait
     static_for<0, 2 * NM>([&](auto qc) {
       constexpr int q0 = decltype(qc)::value;
       multiply_one(cur, qc);
       __builtin_amdgcn_sched_barrier(0);
-      static_for<q0 * 2 * NF / (2 * NM), (q0 + 1) * 2 * NF / (2 * NM)>([&](auto rc) { read_one(nxt, rc, nbuf); });
-      static_for<q0 * C::PER / (2 * NM), (q0 + 1) * C::PER / (2 * NM)>([&](auto cc) { copy_one(cc, buf); });
+      if constexpr (q0 < BAR) {
+        static_for<q0 * 2 * NF / BAR, (q0 + 1) * 2 * NF / BAR>([&](auto rc) { read_one(nxt, rc, nbuf); });
+        static_for<q0 * C::PER / BAR, (q0 + 1) * C::PER / BAR>([&](auto cc) { copy_one(cc, buf); });
+      }
+      if constexpr (q0 == BAR - 1) {
+        wait_vmcnt<(C::NST - 2) * C::PER>();
+        wait_lgkm0();
+        if constexpr (C::NQ > 1) block_barrier();
+      }
       __builtin_amdgcn_sched_barrier(0);
     });
     copy_next();
-    wait_vmcnt<(C::NST - 2) * C::PER>();
-    wait_lgkm0();
-    if constexpr (C::NQ > 1) block_barrier();
     buf = nbuf;
     fold(i);
   };
@@ -337,7 +342,10 @@ __device__ __forceinline__ void slice_body(const SliceArgs& g, Ell ell, int tile
   __syncthreads();
   const ModReducer mod(g.modulus ? g.modulus : 1);
   const int L4 = (lane & 15) * 4;
-  for (int ch = grp; ch < C::NV / 4; ch += C::WK) {
+#pragma unroll
+  for (int c = 0; c < (C::NV / 4 + C::WK - 1) / C::WK; ++c) {
+    const int ch = grp + c * C::WK;
+    if (C::NV / 4 % C::WK != 0 && ch >= C::NV / 4) break;
     const int v = ch * 4 + (lane >> 4);
     v4i w = {0, 0, 0, 0};
 #pragma unroll
@@ -386,6 +394,96 @@ __global__ __launch_bounds__(C::THREADS, 1) void slice_group_kernel(SliceGroupAr
   static_assert(kGroupProducts == 4, "the fold coefficients below");
   const int32_t l0 = jb.ell[0], l1 = jb.ell[1], l2 = jb.ell[2], l3 = jb.ell[3];
   slice_body<C>(g, [=](int p) { return p == 0 ? l0 : p == 1 ? l1 : p == 2 ? l2 : l3; }, blockIdx.x - j * ga.tiles, 0);
+}
+
+// ---------------------------------------------------------------------------
+// The whole of Alg. 1 in one kernel, for products so small that launches and the trip of the planes
+// through memory are their time: a workgroup encodes its 32 rows of A and 32 columns of B into LDS in
+// the stored plane layout, one brick per wave (W waves: W / 2 k-steps of either side), and its waves
+// share out the products and k-steps; their int32 sums meet in LDS as above.  Every tile encodes its
+// own operands, about 2 us of the kernel, so it serves reductions of one brick per wave and outputs of
+// one round of tiles: with a second chunk of the reduction (512^3 on 8 waves) it took 11.4 us
+// against 10.3 for encoder and GEMM, and at 1024^2 x 256, four rounds, 24.5 against 13.2.  AWE6 256^3:
+// 7.2 us against 10.0, 512^2 x 256 7.4 against 9.6, {0, +-1} x INT8 700 x 300 x 200 8.9 against 11.3.
+// E2M3 planes, slower to pack, gain nothing (9.2 against 9.1 at 256^3).
+// ---------------------------------------------------------------------------
+constexpr int kDirectPlanes = 12;  // planes of both sides whose bricks fit the LDS (16 waves: 96 KiB)
+struct DirectArgs {
+  EncodeArgs a, b;
+  LutArg lut_a, lut_b;
+  SliceArgs g;
+};
+
+// LDS: the planes of both sides (or, at the end, the sums), the B side's transpose tiles, the tables.
+constexpr int direct_plane_bytes(int W) { return W / 2 * kBrickBytes; }
+constexpr int direct_sum_bytes(int W) { return W * 16 * 64 * 4; }
+inline int direct_lds(int W, int planes) {
+  return std::max(planes * direct_plane_bytes(W), direct_sum_bytes(W)) + W / 2 * 32 * kTileCol + 2 * 256 * 4;
+}
+
+template <int W>
+__global__ __launch_bounds__(64 * W) void direct_kernel(DirectArgs d) {
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  const SliceArgs& g = d.g;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int KST = W / 2, PB = direct_plane_bytes(W);
+  const int plane_bytes = max((d.a.nplanes + d.b.nplanes) * PB, direct_sum_bytes(W));
+  uint32_t* const luts = reinterpret_cast<uint32_t*>(smem + plane_bytes + KST * 32 * kTileCol);
+  if (threadIdx.x < 512) luts[threadIdx.x] = threadIdx.x < 256 ? d.lut_a.v[threadIdx.x] : d.lut_b.v[threadIdx.x - 256];
+  int tm, tn;
+  slice_tile(g, blockIdx.x, tm, tn);
+  __syncthreads();
+  {
+    const bool side_a = wave < KST;
+    const int i = side_a ? wave : wave - KST;  // the k-step this wave encodes
+    const int np = side_a ? d.a.nplanes : d.b.nplanes;
+    uint8_t* const mine = smem + (side_a ? 0 : d.a.nplanes * PB) + i * kBrickBytes + lane * 16;
+    uint32_t e[32], w[8][4];
+    if (side_a)
+      brick_codes<false>(d.a, tm, i, luts, nullptr, e);
+    else
+      brick_codes<true>(d.b, tn, i, luts + 256, smem + plane_bytes + i * (32 * kTileCol), e);
+    uint32_t bad = 0;
+#pragma unroll
+    for (int j = 0; j < 32; ++j) bad |= e[j];
+    if ((bad & kLutInvalid) && d.a.flag != nullptr) atomicOr(d.a.flag, 1);
+    pack_e2m1_planes<8>(e, w);
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      if (p >= np) break;
+      *reinterpret_cast<uint4*>(mine + p * PB) = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+    }
+  }
+  __syncthreads();
+  // this wave's share of the (product, k-step) units
+  const int steps = (int)d.a.KS, U = g.r * steps, u1 = (wave + 1) * U / W;
+  int32_t iacc[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) iacc[v] = 0;
+  for (int u = wave * U / W; u < u1;) {
+    const int p = u / steps, k0 = u - p * steps, n = min(u1, (p + 1) * steps) - u;
+    const uint8_t* fa = smem + (int)((g.pidx_a >> (4 * p)) & 15u) * PB + k0 * kBrickBytes + lane * 16;
+    const uint8_t* fb = smem + (d.a.nplanes + (int)((g.pidx_b >> (4 * p)) & 15u)) * PB + k0 * kBrickBytes + lane * 16;
+    v16f acc = {0.0f};
+    for (int i = 0; i < n; ++i) mfma_block(acc, frag(fa + i * kBrickBytes), frag(fb + i * kBrickBytes));
+    u += n;
+    const int32_t l = g.ell[p];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) iacc[v] += __mul24(l, (int32_t)acc[v]);
+  }
+  __syncthreads();
+  int32_t* const sums = reinterpret_cast<int32_t*>(smem);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) sums[(wave * 16 + v) * 64 + lane] = iacc[v];
+  __syncthreads();
+  if (wave >= 4) return;
+  const ModReducer mod(g.modulus ? g.modulus : 1);
+  const int L4 = (lane & 15) * 4, v = wave * 4 + (lane >> 4);
+  v4i t = {0, 0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < W; ++k) t += *reinterpret_cast<const v4i*>(sums + (k * 16 + v) * 64 + L4);
+  slice_store(g, mod, tm * 32 + 8 * (v >> 2) + 4 * (L4 >> 5) + (v & 3), tn * 32 + (L4 & 31), t);
 }
 
 // Zeroes C before the parts of split tiles add into it, as words of 4 bytes: row_words per row,
@@ -502,7 +600,26 @@ void fill_slice_args(const GemmLaunch& L, SliceArgs& g) {
   g.outer = L.outer;
 }
 
-}  // namespace
+template <int W>
+awe_status launch_direct_waves(DirectArgs& d, hipStream_t stream) {
+  SliceArgs& g = d.g;
+  g.tiles_m = (g.M + 31) / 32;
+  g.tiles_n = (g.N + 31) / 32;
+  g.split = 1;
+  static std::mutex mu;
+  static std::set<int> done;
+  const awe_status st =
+      set_lds_limit(reinterpret_cast<const void*>(&direct_kernel<W>), direct_lds(W, kDirectPlanes), mu, done);
+  if (st != AWE_OK) return st;
+  hipLaunchKernelGGL(direct_kernel<W>, dim3((unsigned)(g.tiles_m * g.tiles_n)), dim3(64 * W),
+                     direct_lds(W, d.a.nplanes + d.b.nplanes), stream, d);
+  const hipError_t err = hipGetLastError();
+  if (err != hipSuccess) {
+    set_error(std::string("direct product launch: ") + hipGetErrorString(err));
+    return AWE_ERR_HIP;
+  }
+  return AWE_OK;
+}
 
 // The variants' tiles and times on one MI355X: a tile takes about fixed + per_index * r K microseconds
 // (r products, K reduction indices), by format, a round of tiles on all CUs that long, and a launch
@@ -517,19 +634,27 @@ constexpr VariantCost kVariants[] = {
     {32, 32, 3.0, {0.29, 0.38}},   {32, 64, 4.3, {0.385, 0.50}}, {64, 32, 4.3, {0.375, 0.48}},
 };
 
+// Whether the environment asks for particular tile configurations or splits.
+bool tuning_overrides() {
+  for (const char* name : {"AWE_GEMM_CFG", "AWE_GEMM_CFG_E2M3", "AWE_GEMM_CFG_SHARED", "AWE_GEMM_ALLPAIRS",
+                           "AWE_GEMM_CUS", "AWE_GEMM_SPLIT", "AWE_GEMM_SLICE"})
+    if (tuning(name)) return true;
+  return false;
+}
+
+}  // namespace
+
 Slice choose_slice(const GemmLaunch& L, int cus, double tile_us) {
   if (L.flat.r == 0) return Slice{0, 1};
   // AWE_GEMM_SLICE: 0 none, 1 .. 6 that variant (AWE_GEMM_SLICE_SPLIT workgroups per tile); the
   // overrides of the tile configurations leave none.  They change no result.
-  if (const char* e = getenv("AWE_GEMM_SLICE")) {
+  if (const char* e = tuning("AWE_GEMM_SLICE")) {
     const int v = atoi(e);
-    const char* sp = getenv("AWE_GEMM_SLICE_SPLIT");
+    const char* sp = tuning("AWE_GEMM_SLICE_SPLIT");
     const int split = sp && !L.modulus ? atoi(sp) : 1;
     return Slice{v >= 1 && v <= 6 ? v : 0, split >= 1 && split <= 64 ? split : 1};
   }
-  for (const char* name : {"AWE_GEMM_CFG", "AWE_GEMM_CFG_E2M3", "AWE_GEMM_CFG_SHARED", "AWE_GEMM_ALLPAIRS",
-                           "AWE_GEMM_CUS", "AWE_GEMM_SPLIT"})
-    if (getenv(name)) return Slice{0, 1};
+  if (tuning_overrides()) return Slice{0, 1};
   const int64_t len = L.k_end - L.k_begin;
   const double rk = (double)L.flat.r * (double)len, outs = (double)L.M * (double)L.N;
   Slice best{0, 1};
@@ -558,8 +683,8 @@ Slice choose_slice(const GemmLaunch& L, int cus, double tile_us) {
 }
 
 int choose_slice_group(const GemmLaunch* L, int n, int cus, double tile_us) {
-  if (const char* e = getenv("AWE_GEMM_SLICE")) return atoi(e) >= 1 && atoi(e) <= 6 ? atoi(e) : 0;
-  if (getenv("AWE_GEMM_CFG")) return 0;
+  if (const char* e = tuning("AWE_GEMM_SLICE")) return atoi(e) >= 1 && atoi(e) <= 6 ? atoi(e) : 0;
+  if (tuning("AWE_GEMM_CFG")) return 0;
   int best = 0;
   for (int v = 0; v < 6; ++v) {
     const VariantCost& c = kVariants[v];
@@ -606,6 +731,32 @@ awe_status launch_slice_group(const GemmLaunch* L, const int* order, int n, int 
     case 5: return launch_slice_jobs<Slice32x64<0>>(ga, n, stream);
     default: return launch_slice_jobs<Slice64x32<0>>(ga, n, stream);
   }
+}
+
+bool choose_direct(const GemmLaunch& L, int cus) {
+  const EncodeLaunch* a = L.operands;
+  if (!a || !a->other || L.flat.r == 0 || L.fmt != kFmtE2M1 || a->wide || a->nplanes8 || a->other->nplanes8 || a->fp6 ||
+      a->nplanes + a->other->nplanes > kDirectPlanes)
+    return false;
+  if (L.k_begin != 0 || L.k_end < L.K || L.accumulate || L.k_end > 512) return false;
+  const int64_t tiles = ((L.M + 31) / 32) * ((L.N + 31) / 32);
+  if (tiles > 64 * cus) return false;
+  if (const char* e = tuning("AWE_GEMM_DIRECT")) return atoi(e) != 0;
+  if (tuning_overrides()) return false;
+  // (two rounds' worth on 8 waves, whose 60 KiB of LDS let two workgroups share a CU: 1024 x 512 x
+  // 256 9.1 us against 10.6)
+  return tiles <= (L.k_end <= 256 ? 2 : 1) * cus;
+}
+
+awe_status launch_direct(const GemmLaunch& L, hipStream_t stream) {
+  DirectArgs d{};
+  const EncodeLaunch &a = *L.operands, &b = *a.other;
+  encode_args(a, d.a);
+  encode_args(b, d.b);
+  std::copy(a.lut, a.lut + 256, d.lut_a.v);
+  std::copy(b.lut, b.lut + 256, d.lut_b.v);
+  fill_slice_args(L, d.g);
+  return L.k_end <= 256 ? launch_direct_waves<8>(d, stream) : launch_direct_waves<16>(d, stream);
 }
 
 awe_status launch_slice(const GemmLaunch& L, Slice s, hipStream_t stream) {

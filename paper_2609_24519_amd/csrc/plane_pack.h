@@ -55,4 +55,18 @@ __device__ __forceinline__ void pack_e2m1_planes(const uint32_t (&e)[32], uint32
     for (int w = 0; w < 4; ++w) d[p][w] = (p & 1) ? py[w][p >> 1] : px[w][p >> 1];
 }
 
+// One lane's 32 elements of an E2M3 plane: e[j] holds plane p's 6-bit code in bits 8p .. 8p + 5; d
+// receives the 192-bit word with element j in bits 6j .. 6j + 5.
+__device__ __forceinline__ void pack_e2m3_plane(const uint32_t (&e)[32], int p, uint32_t (&d)[6]) {
+#pragma unroll
+  for (int q = 0; q < 6; ++q) d[q] = 0;
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    const uint32_t c = (e[j] >> (8 * p)) & 0x3fu;
+    const int bit = 6 * j;
+    d[bit >> 5] |= c << (bit & 31);
+    if ((bit & 31) > 26) d[(bit >> 5) + 1] |= c >> (32 - (bit & 31));
+  }
+}
+
 }  // namespace awe

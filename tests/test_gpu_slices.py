@@ -100,3 +100,54 @@ def test_chosen_route_on_mixed_shapes():
                          (awe.ENC_FP6P4, 130, 900, 700), (awe.ENC_TERNARY, 1, 5000, 300), (awe.ENC_AWE4, 2100, 1900, 300)]:
         A, B = _operands(enc, M, N, K, M)
         assert np.array_equal(_product(enc, A, B, torch.int32), oracle_gemm.gemm_i64(A, B)), (enc, M, N, K)
+
+
+@pytest.mark.parametrize("enc", [awe.ENC_AWE6, awe.ENC_AWE6ALT, awe.ENC_AWE4, awe.ENC_B13, awe.ENC_TERNARY])
+@pytest.mark.parametrize("K", [1, 64, 65, 255, 256, 257, 512])
+def test_small_products_in_one_kernel(monkeypatch, enc, K):
+    # encode, products and reconstruction in one launch (one brick per wave: 8 waves up to K = 256, 16 up
+    # to 512), against the oracle and against the separate launches; unaligned rows, ldc > N, both
+    # output types
+    for M, N, out in [(1, 1, torch.int32), (33, 31, torch.int64), (64, 96, torch.int32)]:
+        A, B = _operands(enc, M, N, K, K + M)
+        ref = oracle_gemm.gemm_i64(A, B)
+        dA = torch.full((M, K + 3), 127, dtype=torch.int8, device=device())
+        dB = torch.full((K, N + 5), 127, dtype=torch.int8, device=device())
+        dA[:, :K], dB[:, :N] = to_dev(A), to_dev(B)
+        ws_n = awe.workspace_bytes(enc, 0, M, N, K)
+        ws = torch.empty(max(ws_n, 1), dtype=torch.uint8, device=device())
+        flag = torch.zeros(1, dtype=torch.int32, device=device())
+        for direct in ("1", "0"):
+            monkeypatch.setenv("AWE_GEMM_DIRECT", direct)
+            C = torch.full((M, N + 2), -7, dtype=out, device=device())
+            awe.gemm_exact(enc, M, N, K, dA, K + 3, dB, N + 5, C, N + 2, awe.I64 if out == torch.int64 else awe.I32,
+                           ws, ws_n, flag)
+            C = C.cpu().numpy()
+            assert np.array_equal(C[:, :N].astype(np.int64), ref) and (C[:, N:] == -7).all(), (M, N, direct)
+            assert flag.item() == 0
+
+
+@pytest.mark.parametrize("m,K", [(7, 256), (89, 300), (157, 512)])
+def test_small_residue_products_in_one_kernel(monkeypatch, m, K):
+    monkeypatch.setenv("AWE_GEMM_DIRECT", "1")
+    A, B = inputs.residue_pair(70, 45, K, m)
+    assert np.array_equal(awe.matmul_mod(m, to_dev(A), to_dev(B)).cpu().numpy(), oracle_gemm.gemm_mod(m, A, B))
+
+
+@pytest.mark.parametrize("side", ["a", "b"])
+def test_small_product_range_flag(side):
+    A, B = inputs.int8_pair(40, 50, 100, 1, (-8, 7))
+    flag = torch.zeros(1, dtype=torch.int32, device=device())
+    awe.matmul_exact(to_dev(A), to_dev(B), awe.ENC_AWE4, d_range_flag=flag)
+    assert flag.item() == 0
+    t, u = inputs.int8_pair(40, 50, 100, 1, (-1, 1))
+    bad = A.copy()
+    bad[39, 99] = 8  # past int4
+    awe.matmul_exact(to_dev(bad if side == "a" else t), to_dev(B if side == "a" else u),
+                     awe.ENC_AWE4 if side == "a" else awe.ENC_TERNARY, d_range_flag=flag)
+    assert (flag.item() != 0) == (side == "a")
+    flag.zero_()
+    r = np.full((100, 50), 6, np.uint8)
+    r[99, 49] = 7  # past the residues of 7
+    awe.matmul_mod(7, to_dev(np.zeros((40, 100), np.uint8)), to_dev(r), d_range_flag=flag)
+    assert flag.item() != 0
