@@ -406,27 +406,28 @@ __device__ __forceinline__ void load_stage(const GemmArgs& g, const Cursor& c, u
   load_stage_b<C>(g, c, stage_lds, tn, wave, lane);
 }
 
-// Copy q of this wave's share of a stage (one copy per unit): q < A_PW is its A unit q, then
-// its B units, in the order load_stage issues them.
+// Copy Q of this wave's share of a stage: its A units' copies, then its B units', in the order
+// load_stage issues them (every wave has as many: no wave with an extra B unit).
 template <class C, int Q>
 __device__ __forceinline__ void load_one(const GemmArgs& g, const Cursor& c, uint32_t stage_lds, int tm,
                                          int tn, int wave, int lane) {
-  static_assert(C::COPIES == 1, "one copy per unit");
+  static_assert(C::B_XTRA == 0, "as many copies for every wave");
   const uint32_t voff = lane * 16;
-  if constexpr (Q < C::A_PW) {
+  constexpr int h = Q % C::COPIES, unit = Q / C::COPIES;
+  if constexpr (unit < C::A_PW) {
     const int ka = (int)((g.pidx_a >> (4 * c.p)) & 15u);
-    const int id = copy_unit<C>(true, wave, Q);
+    const int id = copy_unit<C>(true, wave, unit);
     const UnitPos u = unit_pos<C>(true, id);
     const int rb = min(tm * (C::BM / kBrickRows) + u.rb, g.rba - 1);
-    dma_brick(g.pa + (int64_t)ka * g.stride_a + stage_global<C>(c.t, g.rba) + unit_global<C>(u, rb, g.rba, g.stride_a, 0), voff,
-              stage_lds + unit_lds<C>(true, id, 0));
+    dma_brick(g.pa + (int64_t)ka * g.stride_a + stage_global<C>(c.t, g.rba) + unit_global<C>(u, rb, g.rba, g.stride_a, h), voff,
+              stage_lds + unit_lds<C>(true, id, h));
   } else {
     const int kb = (int)((g.pidx_b >> (4 * c.p)) & 15u);
-    const int id = copy_unit<C>(false, wave, Q - C::A_PW);
+    const int id = copy_unit<C>(false, wave, unit - C::A_PW);
     const UnitPos u = unit_pos<C>(false, id);
     const int cb = min(tn * (C::BN / kBrickRows) + u.rb, g.rbb - 1);
-    dma_brick(g.pb + (int64_t)kb * g.stride_b + stage_global<C>(c.t, g.rbb) + unit_global<C>(u, cb, g.rbb, g.stride_b, 0), voff,
-              stage_lds + unit_lds<C>(false, id, 0));
+    dma_brick(g.pb + (int64_t)kb * g.stride_b + stage_global<C>(c.t, g.rbb) + unit_global<C>(u, cb, g.rbb, g.stride_b, h), voff,
+              stage_lds + unit_lds<C>(false, id, h));
   }
 }
 
@@ -436,6 +437,18 @@ struct Frags {
   // plane pl's fragments at pl * BMW (pl * BNW); 16x16x128: one per 16-row block
   v8i a[C::MF == 16 ? C::AM : C::SPA * C::BMW], b[C::MF == 16 ? C::AN : C::SPB * C::BNW];
 };
+
+// Fragment R of a k-step: the A fragments of every plane, then the B fragments.
+template <class C, int R>
+__device__ __forceinline__ void read_frag_one(Frags<C>& f, const uint8_t* stage, int ks, int wm, int wn, int lane) {
+  const int i = ks % C::UK;
+  constexpr int NA = C::SPA * C::BMW;
+  if constexpr (R < NA)
+    f.a[R] = frag_fmt<C::FMT>(stage + frag_unit<C>(true, R / C::BMW, wm * C::BMW + R % C::BMW, ks), i, lane);
+  else
+    f.b[R - NA] = frag_fmt<C::FMT>(
+        stage + frag_unit<C>(false, (R - NA) / C::BNW, wn * C::BNW + (R - NA) % C::BNW, ks), i, lane);
+}
 
 template <class C>
 __device__ __forceinline__ void read_frags(Frags<C>& f, const uint8_t* stage, int ks, int wm,
@@ -874,6 +887,26 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
     // stage s+1 has landed and this wave's reads of stage s are done (all of them
     // were issued by then), barrier, refill stage s's buffer with stage s+NSTAGE.
     // The barrier sits between two groups of MFMAs.
+    constexpr bool SPREAD = PD > 0 && C::MF == 32 && !C::AP && C::B_XTRA == 0;
+    constexpr int NQ = C::NPL * C::NPL * C::BMW * C::BNW;                // MFMAs per k-step
+    constexpr int NRD = C::SPA * C::BMW + C::SPB * C::BNW;               // fragments per k-step
+    constexpr int NCOPY = (C::A_PW + C::B_LO) * C::COPIES;               // copies per wave and stage
+    static_assert(!SPREAD || NRD <= NQ, "one fragment read per MFMA");
+    [[maybe_unused]] auto mfma_q = [&](const Frags<C>& cur, auto qc) {
+      constexpr int q = decltype(qc)::value, pair = q / (C::BMW * C::BNW), i = q / C::BNW % C::BMW, j = q % C::BNW;
+      if constexpr (C::MF == 16)
+        static_assert(C::MF != 16 || q >= 0, "not used for 16x16x128");
+      else if constexpr (C::NPL == 2)  // the four plane pairs, each block's MFMAs four apart in issue order
+        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.a[(pair >> 1) * C::BMW + i],
+                                                                    cur.b[(pair & 1) * C::BNW + j], acc[i][j], 2, 2, 0,
+                                                                    (int)g.sa[pair >> 1], 0, (int)g.sb[pair & 1]);
+      else if constexpr (C::FMT == 0)
+        mfma_block(acc[i][j], cur.a[i], cur.b[j]);
+      else if constexpr (C::FMT == 1)
+        mfma_block8(acc[i][j], cur.a[i], cur.b[j]);
+      else
+        mfma_block6(acc[i][j], cur.a[i], cur.b[j]);
+    };
     int buf = 0;
     for (int cs = t_beg; cs < t_end; cs += g.ts) {
       const int ce = min(cs + g.ts, t_end);
@@ -881,6 +914,38 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
         for (int t = cs; t < ce; ++t) {
           const uint32_t cur_off = buf * C::STAGE_BYTES;
           const int nbuf = buf + 1 == NSTAGE ? 0 : buf + 1;
+          if constexpr (SPREAD) {
+            // after each MFMA one fragment read of a later k-step, and the copies that refill stage
+            // s's buffer one by one between the MFMAs from the barrier to the end of the stage
+            // (issued all at once behind the barrier, the eight waves' copies queued at the address
+            // unit with no matrix work in flight: E2M3 with the weights in the scales 159 us at 4096^3
+            // against 137 now and 1030 / 954 at 8192^3, config 5 193 / 186 at 4096^3)
+            static_for<0, C::KSTEPS>([&](auto kc) {
+              constexpr int ks = decltype(kc)::value, kr = ks + PD, BK = C::KSTEPS - PD;
+              if constexpr (ks == BK) {
+                wait_stages<C, NSTAGE - 2>(wave);
+                wait_lgkm0();
+                block_barrier();
+              }
+              const uint8_t* rd = smem + (kr < C::KSTEPS ? cur_off : nbuf * C::STAGE_BYTES);
+              static_for<0, NQ>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                mfma_q(f[ks % NSETS], qc);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (q < NRD) read_frag_one<C, q>(f[kr % NSETS], rd, kr % C::KSTEPS, wm, wn, lane);
+                if constexpr (ks >= BK) {
+                  constexpr int slot = (ks - BK) * NQ + q, slots = PD * NQ;
+                  static_for<slot * NCOPY / slots, (slot + 1) * NCOPY / slots>([&](auto cc) {
+                    load_one<C, decltype(cc)::value>(g, nxt, lds0 + cur_off, tm, tn, wave, lane);
+                  });
+                }
+                __builtin_amdgcn_sched_barrier(0);
+              });
+            });
+            cursor_next(nxt, g, t_end);
+            buf = nbuf;
+            continue;
+          }
 #pragma unroll
           for (int ks = 0; ks < C::KSTEPS; ++ks) {
             if (ks == C::KSTEPS - PD) {
