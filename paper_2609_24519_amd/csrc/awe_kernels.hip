@@ -584,10 +584,11 @@ __global__ __launch_bounds__(256) void zero_tiles_kernel(GemmArgs g, int bm, int
 }
 
 // One workgroup's output tile over reduction stages t_beg .. t_end - 1 (part >= 0: one
-// part of a split tile, added into C).  fold_coef(p): the fold coefficient of product p.
+// part of a split tile, added into C).  fold_coef(p): the fold coefficient of product p.  BYTES: C
+// is residues as bytes (otherwise g.modulus and g.c64 say).
 // The arguments come by value: through a reference the compiler keeps more of them live
 // (the 256 x 192 tiles then spill).
-template <class C, bool ROWS16, class FoldCoef>
+template <class C, bool BYTES, class FoldCoef>
 __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int tile, int part, int t_beg,
                                           int t_end) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -1036,8 +1037,10 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
   // the MFMA: 32x32 blocks, lane L holds rows 8 (v / 4) + 4 (L / 32) + v % 4 of column L % 32;
   // 16x16 blocks, rows 4 (L / 16) + v of column L % 16.
   constexpr int BS = C::MF;  // rows and columns of an accumulator block
-  const int row0 = tm * C::BM + wm * (32 * C::BMW) + (BS == 16 ? 4 * (lane >> 4) : 4 * (lane >> 5));
-  const int col0 = tn * C::BN + wn * (32 * C::BNW) + (lane & (BS - 1));
+  // (the lane anew: kept from the start it would hold a register through the loop)
+  const int elane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int row0 = tm * C::BM + wm * (32 * C::BMW) + (BS == 16 ? 4 * (elane >> 4) : 4 * (elane >> 5));
+  const int col0 = tn * C::BN + wn * (32 * C::BNW) + (elane & (BS - 1));
   auto emit = [&](int i, int j, int v, int32_t val) {
     const int row = row0 + i * BS + (BS == 16 ? v : 8 * (v >> 2) + (v & 3)), col = col0 + j * BS;
     if (part < 0)
@@ -1045,28 +1048,54 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
     else
       add_output(g, row, col, val);
   };
-  if constexpr (ROWS16 && C::MF == 32 && !C::OUTG && C::FMT == 0 && C::NPL == 1) {
-    // Whole tiles written (not added) as int32 or int64: each 32 x 32 block goes through a
-    // per-wave LDS slot (rows of 36 words, 16-byte aligned) so that a lane stores 16 bytes of
+  if constexpr (C::MF == 32 && !C::OUTG && C::FMT == 0 && C::NPL == 1) {
+    // Whole tiles written (not added): each 32 x 32 block goes through a
+    // per-wave LDS slot (rows of 36 words, 16-byte aligned) so that a elane stores 16 bytes of
     // one row (4 outputs) instead of 16 single outputs of one column: a quarter of the store
     // instructions.  Uniform per workgroup.
     static_assert(C::NW * 32 * 36 * 4 <= C::NSTAGE * C::STAGE_BYTES, "row slots inside the ring");
-    const bool rows16 = part < 0 && !g.modulus && !g.accumulate && (tm + 1) * C::BM <= g.M &&
-                        (tn + 1) * C::BN <= g.N && (g.ldc & 3) == 0 &&
-                        (reinterpret_cast<uintptr_t>(g.C) & 15) == 0;
+    const bool bytes = BYTES || g.c64 == 2;
+    const bool rows16 = part < 0 && !g.accumulate && (tm + 1) * C::BM <= g.M && (tn + 1) * C::BN <= g.N &&
+                        (g.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(g.C) & (bytes ? 3 : 15)) == 0;
     if (rows16) {
       block_barrier();  // every wave is past its last ring read, and its last copies have landed
       int32_t* const slot = reinterpret_cast<int32_t*>(smem) + wave * (32 * 36);
-      const int rr = lane >> 3, cc = (lane & 7) * 4;  // read: rows rr + 8 q, columns cc .. cc + 3
-      auto put_block = [&](int i, int j, auto value) {
+      const int rr = elane >> 3, cc = (elane & 7) * 4;  // read: rows rr + 8 q, columns cc .. cc + 3
+      // every block through the slot, four columns of a row at a time to store(offset in C, values)
+      auto put_blocks = [&](auto store) {
+        auto put_block = [&](int i, int j, auto value) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) slot[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * 36 + (lane & 31)] = value(v);
+          for (int v = 0; v < 16; ++v) slot[(8 * (v >> 2) + 4 * (elane >> 5) + (v & 3)) * 36 + (elane & 31)] = value(v);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const v4i w = *reinterpret_cast<const v4i*>(slot + (rr + 8 * q) * 36 + cc);
-          const int64_t off =
-              (int64_t)(tm * C::BM + wm * (32 * C::BMW) + i * 32 + rr + 8 * q) * g.ldc + tn * C::BN +
-              wn * (32 * C::BNW) + j * 32 + cc;
+          for (int q = 0; q < 4; ++q) {
+            const v4i w = *reinterpret_cast<const v4i*>(slot + (rr + 8 * q) * 36 + cc);
+            store((int64_t)(tm * C::BM + wm * (32 * C::BMW) + i * 32 + rr + 8 * q) * g.ldc + tn * C::BN +
+                      wn * (32 * C::BNW) + j * 32 + cc,
+                  w);
+          }
+        };
+#pragma unroll
+        for (int b = 0; b < NREG; ++b)
+          put_block(b / C::AN, b % C::AN, [&](int v) { return iacc[b / C::AN][b % C::AN][v]; });
+#pragma unroll
+        for (int b = NREG; b < C::AM * C::AN; ++b)
+          put_block(b / C::AN, b % C::AN, [&](int v) { return fold_lds[((b - NREG) * C::AV + v) * 64]; });
+      };
+      if (BYTES || g.modulus) {
+        const ModReducer mod(g.modulus);
+        put_blocks([&](int64_t off, v4i w) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[e] = mod(w[e]);
+          if (bytes)
+            __builtin_nontemporal_store((uint32_t)(w[0] | (w[1] << 8) | (w[2] << 16) | (w[3] << 24)),
+                                        reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(g.C) + off));
+          else
+            __builtin_nontemporal_store(w, reinterpret_cast<v4i*>(reinterpret_cast<int32_t*>(g.C) + off));
+        });
+        return;
+      }
+      if constexpr (!BYTES)
+        put_blocks([&](int64_t off, v4i w) {
           if (g.c64) {
             typedef long long v2l __attribute__((ext_vector_type(2)));
             v2l lo, hi;
@@ -1083,14 +1112,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
             for (int e = 0; e < 4; ++e) t[e] = (int32_t)((int64_t)(w[e] >> g.log2D) * g.outer);
             __builtin_nontemporal_store(t, reinterpret_cast<v4i*>(reinterpret_cast<int32_t*>(g.C) + off));
           }
-        }
-      };
-#pragma unroll
-      for (int b = 0; b < NREG; ++b)
-        put_block(b / C::AN, b % C::AN, [&](int v) { return iacc[b / C::AN][b % C::AN][v]; });
-#pragma unroll
-      for (int b = NREG; b < C::AM * C::AN; ++b)
-        put_block(b / C::AN, b % C::AN, [&](int v) { return fold_lds[((b - NREG) * C::AV + v) * 64]; });
+        });
       return;
     }
   }
@@ -1113,7 +1135,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
         }
     return;
   }
-  if (g.modulus) {  // residues, whose tiles are never split
+  if (BYTES || g.modulus) {  // residues, whose tiles are never split
     const ModReducer mod(g.modulus);
     auto residues = [&](auto store) {
       auto emit_r = [&](int i, int j, int v, int32_t val) {
@@ -1128,7 +1150,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
 #pragma unroll
         for (int v = 0; v < C::AV; ++v) emit_r(b / C::AN, b % C::AN, v, fold_lds[((b - NREG) * C::AV + v) * 64]);
     };
-    if (g.c64 == 2)
+    if (BYTES || g.c64 == 2)
       residues([&](int row, int col, int32_t rr) { store_residue_u8(g, row, col, rr); });
     else
       residues([&](int row, int col, int32_t rr) { store_residue(g, row, col, rr); });
@@ -1159,7 +1181,7 @@ __global__ __launch_bounds__(C::THREADS, 1) void gemm_kernel(GemmArgs g) {
     t_end = min(g.t_end, t_beg + per);
     if (t_beg >= t_end) return;  // the host splits only ranges of at least 2 stages per part
   }
-  gemm_tile<C, true>(g, [&](int p) { return g.fold_ell[p]; }, tile, part, t_beg, t_end);
+  gemm_tile<C, false>(g, [&](int p) { return g.fold_ell[p]; }, tile, part, t_beg, t_end);
 }
 
 // Several GEMMs of one shape in one launch (the residue route's moduli): job j's tiles are
@@ -1211,7 +1233,7 @@ __global__ __launch_bounds__(C::THREADS, 1) void gemm_group_kernel(GroupArgs ga)
   static_assert(kGroupProducts == 4, "the fold coefficients below");
   const int32_t f0 = uniform(jb.fold_ell[0]), f1 = uniform(jb.fold_ell[1]), f2 = uniform(jb.fold_ell[2]),
                 f3 = uniform(jb.fold_ell[3]);
-  gemm_tile<C, false>(g, [=](int p) { return p == 0 ? f0 : p == 1 ? f1 : p == 2 ? f2 : f3; }, tile, -1, g.t_begin,
+  gemm_tile<C, true>(g, [=](int p) { return p == 0 ? f0 : p == 1 ? f1 : p == 2 ? f2 : f3; }, tile, -1, g.t_begin,
                g.t_end);
 }
 
@@ -1403,7 +1425,7 @@ template <class C>
 awe_status launch_tile(GemmArgs& g, const GemmLaunch& L, hipStream_t stream) {
   const int64_t tiles_m = (L.M + C::BM - 1) / C::BM, tiles_n = (L.N + C::BN - 1) / C::BN;
   g.t_begin = (int32_t)(L.k_begin / C::KT);
-  g.t_end = (int32_t)(L.k_end / C::KT);
+  g.t_end = (int32_t)((std::min(L.k_end, L.K) + C::KT - 1) / C::KT);  // (not the padding's whole stages)
   g.ts = (int32_t)(L.k_seg / C::KT);
   g.tiles_m = (int32_t)tiles_m;
   g.tiles_n = (int32_t)tiles_n;
@@ -1471,7 +1493,7 @@ awe_status launch_group_tile(const GemmLaunch* L, const int* order, int n, hipSt
     return AWE_ERR_UNSUPPORTED;
   }
   g.t_begin = (int32_t)(L[0].k_begin / C::KT);
-  g.t_end = (int32_t)(L[0].k_end / C::KT);
+  g.t_end = (int32_t)((std::min(L[0].k_end, L[0].K) + C::KT - 1) / C::KT);
   g.tiles_m = (int32_t)tiles_m;
   g.tiles_n = (int32_t)tiles_n;
   g.n_full = (int32_t)tiles;
@@ -1723,8 +1745,7 @@ bool gemm_group_ok(const GemmLaunch* L, int n) {
     if (a.M != L[0].M || a.N != L[0].N || a.K != L[0].K || a.k_begin != L[0].k_begin ||
         a.k_end != L[0].k_end || a.k_end <= a.k_begin)
       return false;
-    if (a.c_type != L[0].c_type || a.c_u8 != L[0].c_u8 || (a.c_u8 && !a.modulus) || a.log2D != L[0].log2D ||
-        a.outer != L[0].outer || a.ldc != L[0].ldc || a.stride_a != L[0].stride_a || a.stride_b != L[0].stride_b)
+    if (!a.c_u8 || !a.modulus || a.log2D != L[0].log2D || a.outer != L[0].outer || a.ldc != L[0].ldc || a.stride_a != L[0].stride_a || a.stride_b != L[0].stride_b)
       return false;
   }
   return true;

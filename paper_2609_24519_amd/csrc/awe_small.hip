@@ -98,6 +98,10 @@ __device__ __forceinline__ void slice_store(const SliceArgs& g, const ModReducer
     for (int e = 0; e < 4; ++e) w[e] = mod(w[e]);
     if (g.c64 == 2) {
       uint8_t* Cp = reinterpret_cast<uint8_t*>(g.C) + off;
+      if (n == 4 && !g.accumulate && (reinterpret_cast<uintptr_t>(Cp) & 3) == 0) {
+        *reinterpret_cast<uint32_t*>(Cp) = (uint32_t)(w[0] | (w[1] << 8) | (w[2] << 16) | (w[3] << 24));
+        return;
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (e < n) {
@@ -580,7 +584,7 @@ void fill_slice_args(const GemmLaunch& L, SliceArgs& g) {
   g.rba = (int32_t)((L.M + kBrickRows - 1) / kBrickRows);
   g.rbb = (int32_t)((L.N + kBrickRows - 1) / kBrickRows);
   g.item0 = (int32_t)(L.k_begin / 128);
-  g.items = (int32_t)((L.k_end - L.k_begin) / 128);
+  g.items = (int32_t)((std::min(L.k_end, L.K) - L.k_begin + 127) / 128);  // (not the padding's whole items)
   g.seg = (int32_t)(L.flat.k_seg / 128);
   g.r = L.flat.r;
   g.pidx_a = g.pidx_b = 0;
