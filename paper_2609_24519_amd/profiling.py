@@ -30,8 +30,10 @@ import os
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-# the GEMM's kernel code and its addressing (tile configurations, copy / LDS / fragment offsets)
-KERNEL_SOURCES = tuple(os.path.join(HERE, "csrc", f) for f in ("awe_kernels.hip", "gemm_layout.h", "plane_pack.h"))
+# the GEMM's and the encoder's kernel code, their shared device helpers and the GEMM's addressing (tile
+# configurations, copy / LDS / fragment offsets)
+KERNEL_SOURCES = tuple(os.path.join(HERE, "csrc", f) for f in ("awe_kernels.hip", "gemm_layout.h", "gemm_device.h",
+                                                               "encode_device.h", "plane_pack.h"))
 COPY_BYTES = 1 << 30  # bench.py --calibrate-copy copies 1 GiB
 
 
@@ -46,12 +48,16 @@ def kernel_source_hash():
 _LABELS = (  # first match wins
     ("residue_encode_kernel<true>", "residue_encode_kernel (B side, transposed)"),
     ("residue_encode_kernel<false>", "residue_encode_kernel (A side)"),
+    ("residue_encode_kernel", "residue_encode_kernel (both operands)"),
     ("residues_kernel", "residues_kernel"),
     ("crt_kernel", "crt_kernel"),
     ("gemm_group_kernel", "gemm_group_kernel"),
+    ("slice_group_kernel", "slice_group_kernel"),
+    ("slice_kernel", "slice_kernel"),
+    ("direct_kernel", "direct_kernel"),
     ("gemm_kernel", "gemm_kernel"),
-    ("encode16_kernel<true>", "encode16_kernel (B side, transposed)"),
-    ("encode16_kernel<false>", "encode16_kernel (A side)"),
+    ("encode16_kernel", "encode16_kernel"),
+    ("encode_pair_kernel", "encode_pair_kernel (both operands)"),
     ("encode_kernel<true>", "encode_kernel (B side, transposed)"),
     ("encode_kernel<false>", "encode_kernel (A side)"),
     ("zero_tiles_kernel", "zero_tiles_kernel"),
