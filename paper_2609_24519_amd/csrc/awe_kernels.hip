@@ -1369,12 +1369,17 @@ GroupChoice choose_group_cfg(const GemmLaunch* L, int n) {
 // Tile configuration for E2M3 operands: AWE_GEMM_CFG_E2M3 (0: 256x128 with 8 waves in
 // 3 stages, 1: as 0 in 4 stages, 3: as 0 with 4 k-steps per stage in 2 stages, 5: 256x192 with
 // 8 waves reading fragments in place and the int32 fold accumulators of 1 of each wave's 6
-// blocks in LDS, 6: as 5 with 2 blocks in LDS and 2 stages) overrides the default 5, the
-// fastest measured at 8192^3 (in one process: 3: 1.16-1.18 ms, 5: 1.07-1.10 ms, 6: 1.24-1.26 ms).
-int choose_cfg_e2m3() {
+// blocks in LDS, 6: as 5 with 2 blocks in LDS and 2 stages) if it names one, else 3 or 5, whichever
+// has its rounds done first, a round of 5 taken as 1.4 rounds of 3.  Measured in one process (3 / 5,
+// us): 2048 x 4096 x 4096 69 / 101, 4096^2 x 2048 79 / 115, 4096^3 133 / 176, 5000 x 4000 x 4096 186 /
+// 198, 8192 x 4096 x 4096 265 / 293, 6144^2 x 4096 322 / 299, 8192^3 1115 / 1008; 3000^3 a tie.
+int choose_cfg_e2m3(const GemmLaunch& L) {
   const char* e = tuning("AWE_GEMM_CFG_E2M3");
   const int forced = e ? atoi(e) : -1;
-  return forced == 0 || forced == 1 || forced == 3 || forced == 6 ? forced : 5;
+  if (forced == 0 || forced == 1 || forced == 3 || forced == 5 || forced == 6) return forced;
+  const int cus = compute_units();
+  const int64_t tm = (L.M + 255) / 256;
+  return 1.4 * rounds(tm * ((L.N + 191) / 192), cus) < rounds(tm * ((L.N + 127) / 128), cus) ? 5 : 3;
 }
 
 // The kernel arguments of one launch.
@@ -1679,7 +1684,8 @@ awe_status launch_gemm(const GemmLaunch& L, hipStream_t stream) {
     else if (L.shared)
       tile_time = tile_split<Cfg8w64x64sh>(L, cus).time;
     else if (L.fmt == kFmtE2M3)
-      tile_time = tile_split<Cfg8w64x96p0lfe2m3>(L, cus).time;
+      tile_time = (choose_cfg_e2m3(L) == 3 ? tile_split<Cfg8w64x64k4e2m3>(L, cus)
+                                           : tile_split<Cfg8w64x96p0lfe2m3>(L, cus)).time;
     else
       tile_time = choose_cfg(L).time;
   }
@@ -1704,7 +1710,7 @@ awe_status launch_gemm(const GemmLaunch& L, hipStream_t stream) {
     return launch_tile<Cfg8w64x64sh>(g, L, stream);
   }
   if (L.fmt == kFmtE2M3) {
-    switch (choose_cfg_e2m3()) {
+    switch (choose_cfg_e2m3(L)) {
       case 1: return launch_tile<Cfg8w64x64s4e2m3>(g, L, stream);
       case 3: return launch_tile<Cfg8w64x64k4e2m3>(g, L, stream);
       case 5: return launch_tile<Cfg8w64x96p0lfe2m3>(g, L, stream);
