@@ -351,6 +351,7 @@ awe_status exact_impl(const Scheme& s, int64_t M, int64_t N, int64_t K, const vo
     if (st != AWE_OK) return st;
     ea.other = &eb;  // one launch for both, with the first of the plan
     plan[0].operands = &ea;
+    plan[0].from_operands = plan.size() == 1;
   }
   for (size_t i = 0; st == AWE_OK && i < plan.size(); ++i) st = launch_gemm(plan[i], stream);
   return st;

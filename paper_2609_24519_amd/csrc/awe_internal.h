@@ -206,8 +206,11 @@ struct GemmLaunch {
   int32_t modulus;
   FlatProducts flat;
   // Both operands, to be encoded into the planes before the products (their launch, nullable: the
-  // planes are there already).  The launcher may multiply straight from them instead.
+  // planes are there already).
   const EncodeLaunch* operands;
+  // The launcher may multiply straight from the operands and leave the planes unwritten: no other
+  // launch of the product reads them.
+  bool from_operands;
 };
 awe_status launch_gemm(const GemmLaunch& g, hipStream_t stream);
 

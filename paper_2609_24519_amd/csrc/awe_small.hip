@@ -739,7 +739,7 @@ awe_status launch_slice_group(const GemmLaunch* L, const int* order, int n, int 
 
 bool choose_direct(const GemmLaunch& L, int cus) {
   const EncodeLaunch* a = L.operands;
-  if (!a || !a->other || L.flat.r == 0 || L.fmt != kFmtE2M1 || a->wide || a->nplanes8 || a->other->nplanes8 || a->fp6 ||
+  if (!a || !L.from_operands || !a->other || L.flat.r == 0 || L.fmt != kFmtE2M1 || a->wide || a->nplanes8 || a->other->nplanes8 || a->fp6 ||
       a->nplanes + a->other->nplanes > kDirectPlanes)
     return false;
   if (L.k_begin != 0 || L.k_end < L.K || L.accumulate || L.k_end > 512) return false;

@@ -3,8 +3,8 @@ sizes, the C ABI's argument checks, the residue set's constants and caches) buil
 under the host sanitizers, the device launchers replaced by counting stubs
 (tests/host_sanitize/launch_stubs.cpp): AddressSanitizer and UndefinedBehaviorSanitizer over
 every encoding and error path (tests/host_sanitize/abi_driver.cpp), ThreadSanitizer over
-eight threads calling the ABI at once (tests/host_sanitize/abi_threads.cpp).  CPU only:
-nothing here touches a GPU."""
+eight threads calling the ABI at once (tests/host_sanitize/abi_threads.cpp), and what the product
+launches may do (tests/host_sanitize/plan_driver.cpp).  CPU only: nothing here touches a GPU."""
 import os
 import shutil
 import subprocess
@@ -51,3 +51,11 @@ def test_host_abi_under_asan_and_ubsan(tmp_path):
 def test_host_abi_threads_under_tsan(tmp_path):
     last = _build_and_run(tmp_path, "abi_threads.cpp", "thread", {"TSAN_OPTIONS": "halt_on_error=1"})
     assert last == ["threads", "8", "failures", "0"], last
+
+
+def test_product_launches(tmp_path):
+    # operands and planes of every launch of awe_gemm_exact and its relatives
+    last = _build_and_run(tmp_path, "plan_driver.cpp", "address,undefined",
+                          {"ASAN_OPTIONS": "detect_leaks=0:abort_on_error=0",
+                           "UBSAN_OPTIONS": "print_stacktrace=1"})
+    assert last[0] == "calls" and int(last[1]) >= 30 and last[-2:] == ["failures", "0"], last
