@@ -31,6 +31,9 @@
  *    (B[k*ldb + j]), C is M x N (C[i*ldc + j]).  Leading dimensions must be
  *    at least the row length.  Empty problems (M or N zero) succeed and write
  *    nothing; K = 0 writes zeros.
+ *  - awe_gemm_exact, awe_gemm_mod and awe_gemm_crt read all of A and B before they write C, so
+ *    C may share memory with an operand (which it then overwrites); outputs share no memory with
+ *    stored planes, a workspace or the range flag.
  *
  * Stored plane layout (the output of awe_encode, the input of
  * awe_gemm_planes).  One side holds P planes back to back; plane p starts at

@@ -322,6 +322,16 @@ awe_status encode_impl(const Scheme& s, awe_side side, const void* x, int64_t ro
   return st != AWE_OK || e.rows == 0 ? st : launch_encode(e, stream);
 }
 
+// First and past the last byte of a row-major matrix.
+struct Extent {
+  uintptr_t begin, end;
+};
+Extent extent(const void* p, int64_t rows, int64_t cols, int64_t ld, int64_t esize) {
+  const uintptr_t b = reinterpret_cast<uintptr_t>(p);
+  return Extent{b, b + ((uintptr_t)(rows - 1) * (uintptr_t)ld + (uintptr_t)cols) * (uintptr_t)esize};
+}
+bool overlap(const Extent& x, const Extent& y) { return x.begin < y.end && y.begin < x.end; }
+
 awe_status exact_impl(const Scheme& s, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
                       const void* B, int64_t ldb, void* C, int64_t ldc, awe_dtype c_type,
                       void* ws, size_t ws_bytes, int32_t* flag, hipStream_t stream) {
@@ -351,7 +361,12 @@ awe_status exact_impl(const Scheme& s, int64_t M, int64_t N, int64_t K, const vo
     if (st != AWE_OK) return st;
     ea.other = &eb;  // one launch for both, with the first of the plan
     plan[0].operands = &ea;
-    plan[0].from_operands = plan.size() == 1;
+    // (C may lie on an operand: with the planes in between, every entry is read before C is written,
+    // while a kernel that multiplies from the operands still reads them as its first tiles are stored)
+    const int64_t esize = s.wide ? 2 : 1;
+    const Extent c = extent(C, M, N, ldc, c_type == AWE_I64 ? 8 : 4);
+    plan[0].from_operands = plan.size() == 1 && !overlap(c, extent(A, M, K, lda, esize)) &&
+                            !overlap(c, extent(B, K, N, ldb, esize));
   }
   for (size_t i = 0; st == AWE_OK && i < plan.size(); ++i) st = launch_gemm(plan[i], stream);
   return st;

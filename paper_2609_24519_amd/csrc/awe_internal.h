@@ -209,7 +209,7 @@ struct GemmLaunch {
   // planes are there already).
   const EncodeLaunch* operands;
   // The launcher may multiply straight from the operands and leave the planes unwritten: no other
-  // launch of the product reads them.
+  // launch of the product reads them, and C shares no memory with an operand.
   bool from_operands;
 };
 awe_status launch_gemm(const GemmLaunch& g, hipStream_t stream);

@@ -151,3 +151,22 @@ def test_small_product_range_flag(side):
     r[99, 49] = 7  # past the residues of 7
     awe.matmul_mod(7, to_dev(np.zeros((40, 100), np.uint8)), to_dev(r), d_range_flag=flag)
     assert flag.item() != 0
+
+
+@pytest.mark.parametrize("where", ["on_a", "on_b", "tail_of_a"])
+def test_small_product_written_over_an_operand(where):
+    # C in an operand's memory: all of A and B is read before C is written
+    M, N, K = 256, 256, 256
+    A, B = _operands(awe.ENC_AWE6, M, N, K, 3)
+    buf = torch.zeros(M * K + 4 * M * N, dtype=torch.uint8, device=device())
+    x = A if where != "on_b" else B
+    at = 0 if where != "tail_of_a" else 1024
+    buf[:M * K] = to_dev(x).reshape(-1).view(torch.uint8)
+    mine = buf[:M * K].view(torch.int8)
+    C = buf[at:at + 4 * M * N].view(torch.int32)
+    ws_n = awe.workspace_bytes(awe.ENC_AWE6, 0, M, N, K)
+    ws = torch.empty(ws_n, dtype=torch.uint8, device=device())
+    a, b = (mine, to_dev(B)) if where != "on_b" else (to_dev(A), mine)
+    awe.gemm_exact(awe.ENC_AWE6, M, N, K, a, K, b, N, C, N, awe.I32, ws, ws_n, None)
+    got = C.cpu().numpy().reshape(M, N).astype(np.int64)
+    assert np.array_equal(got, oracle_gemm.gemm_i64(A, B))
