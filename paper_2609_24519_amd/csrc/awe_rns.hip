@@ -167,8 +167,25 @@ __global__ __launch_bounds__(256) void residues_kernel(const int64_t* __restrict
 constexpr int kLutHalf = 136;  // remainders lie within 129
 constexpr int kLutSize = 2 * kLutHalf;
 
-// Per side and modulus (index m - 2): the table above, uploaded once per device.
+// Per side and modulus (index m - 2): the table above, written once per device.
 __device__ uint32_t g_mod_lut[2][255][kLutSize];
+
+// Some of these tables, from the modulus's packed codes of residues 0 .. m - 1 (plane p in bits
+// 4p .. 4p + 3), one workgroup each.  The codes are kernel arguments: no copy, no host buffer to keep.
+constexpr int kTablesPerLaunch = 7;  // 3.6 KB of arguments
+struct TableArgs {
+  uint16_t code[kTablesPerLaunch][256];
+  uint16_t side[kTablesPerLaunch], m[kTablesPerLaunch];
+};
+__global__ __launch_bounds__(256) void mod_table_kernel(TableArgs t) {
+  const int b = blockIdx.x, m = t.m[b];
+  uint32_t* dst = g_mod_lut[t.side[b]][m - 2];
+  for (int i = threadIdx.x; i < kLutSize; i += 256) {
+    const int r = (i - kLutHalf) % m;
+    const uint32_t c = t.code[b][r < 0 ? r + m : r];
+    dst[i] = (c & 0xfu) | (((c >> 4) & 0xfu) << 8) | (((c >> 8) & 0xfu) << 16);
+  }
+}
 
 struct ResidueSide {
   const int64_t* x;
@@ -445,33 +462,79 @@ awe_status launch_residues(const int64_t* x, int64_t rows, int64_t cols, int64_t
 }
 
 namespace {
-// Uploads the tables of one side's moduli into g_mod_lut on the current device, each once per device
-// (a table depends on its modulus alone): luts[j] holds the packed codes of residues 0 .. m - 1 (plane p
-// in bits 4p .. 4p + 3).
-awe_status ensure_mod_tables(int side, const uint32_t* m, const uint32_t* const* luts, int n) {
+// While it lives, calls of this thread may be ones that a capture of the global kind, open in any thread,
+// would otherwise be invalidated by (none of them touches a capturing stream).
+class RelaxedCapture {
+ public:
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+
+ private:
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
+
+// The tables of g_mod_lut on one device.  They are written on a stream of their own, which waits for
+// no other; `done` is recorded behind the latest, and other streams wait for it until it is seen
+// complete.
+struct ModTables {
+  std::bitset<2 * 255> have;  // side 255 + m - 2: written, or being written before `done`
+  hipStream_t stream = nullptr;
+  hipEvent_t done = nullptr;
+  bool pending = false;  // `done` has not been seen complete
+};
+
+// Makes the tables of both operands' moduli (sides[0] A's, sides[1] B's, nullable) readable by what
+// `stream` is given next, each written once per device (a table depends on its modulus alone).  The
+// host does not wait, unless `stream` is being captured before tables it needs are seen complete: a
+// captured wait could not refer to them.
+hipError_t ensure_mod_tables(const ResidueEncodeArgs* const (&sides)[2], const uint32_t* m, int n, hipStream_t stream) {
   static std::mutex mu;
-  static std::map<int, std::bitset<2 * 255>> loaded;  // per device: side 255 + m - 2
+  static std::map<int, ModTables> devices;
   int dev = 0;
   hipError_t err = hipGetDevice(&dev);
+  if (err != hipSuccess) return err;
   std::lock_guard<std::mutex> lk(mu);
-  std::bitset<2 * 255>& have = loaded[dev];
-  for (int j = 0; j < n && err == hipSuccess; ++j) {
-    const size_t slot = (size_t)side * 255 + (m[j] - 2);
-    if (have[slot]) continue;
-    uint32_t t[kLutSize];
-    for (int i = 0; i < kLutSize; ++i) {
-      const int mj = (int)m[j], r = ((i - kLutHalf) % mj + mj) % mj;
-      const uint32_t c = luts[j][r];
-      t[i] = (c & 0xfu) | (((c >> 4) & 0xfu) << 8) | (((c >> 8) & 0xfu) << 16);
+  ModTables& t = devices[dev];
+  int missing[2 * kMaxModuli], count = 0;  // side n + j
+  for (int s = 0; s < 2; ++s)
+    for (int j = 0; sides[s] && j < n; ++j)
+      if (!t.have[s * 255 + m[j] - 2]) missing[count++] = s * n + j;
+  if (count == 0 && !t.pending) return hipSuccess;
+
+  const RelaxedCapture relaxed;
+  if (count > 0) {
+    if (!t.stream) err = hipStreamCreateWithFlags(&t.stream, hipStreamNonBlocking);
+    if (err == hipSuccess && !t.done) err = hipEventCreateWithFlags(&t.done, hipEventDisableTiming);
+    for (int i = 0; i < count && err == hipSuccess; i += kTablesPerLaunch) {
+      TableArgs a{};
+      const int k = std::min(kTablesPerLaunch, count - i);
+      for (int b = 0; b < k; ++b) {
+        const int s = missing[i + b] / n, j = missing[i + b] % n;
+        a.side[b] = (uint16_t)s;
+        a.m[b] = (uint16_t)m[j];
+        for (uint32_t r = 0; r < m[j]; ++r) a.code[b][r] = (uint16_t)(sides[s]->luts[j][r] & 0xfffu);
+      }
+      hipLaunchKernelGGL(mod_table_kernel, dim3((unsigned)k), dim3(256), 0, t.stream, a);
+      err = hipGetLastError();
     }
-    err = hipMemcpyToSymbol(HIP_SYMBOL(g_mod_lut), t, sizeof(t), sizeof(t) * slot, hipMemcpyHostToDevice);
-    if (err == hipSuccess) have[slot] = true;
+    if (err == hipSuccess) err = hipEventRecord(t.done, t.stream);
+    if (err != hipSuccess) return err;
+    for (int i = 0; i < count; ++i) t.have.set((size_t)(missing[i] / n) * 255 + m[missing[i] % n] - 2);
+    t.pending = true;
+  } else if (hipEventQuery(t.done) == hipSuccess) {
+    t.pending = false;
+    return hipSuccess;
+  } else {
+    (void)hipGetLastError();  // (not ready yet, which the check of the next launch would report)
   }
-  if (err != hipSuccess) {
-    set_error(std::string("residue table upload: ") + hipGetErrorString(err));
-    return AWE_ERR_HIP;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) {
+    err = hipEventSynchronize(t.done);
+    if (err == hipSuccess) t.pending = false;
+    return err;
   }
-  return AWE_OK;
+  return hipStreamWaitEvent(stream, t.done, 0);
 }
 }  // namespace
 
@@ -517,8 +580,6 @@ awe_status launch_residue_encode(const ResidueEncodeArgs& e, const ResidueParams
       o.off[j] = a.off[j];
       g.mod[j].np[s] = a.np[j];
     }
-    const awe_status st = ensure_mod_tables(s, P.m, a.luts, P.n);
-    if (st != AWE_OK) return st;
     blocks[s] = (a.nbricks + 3) / 4;
     bricks += a.nbricks;
   }
@@ -526,6 +587,11 @@ awe_status launch_residue_encode(const ResidueEncodeArgs& e, const ResidueParams
   if (blocks[0] + blocks[1] > (int64_t(1) << 24) - 1) {
     set_error("operands too large for the residue encoder");
     return AWE_ERR_UNSUPPORTED;
+  }
+  hipError_t err = ensure_mod_tables(sides, P.m, P.n, stream);
+  if (err != hipSuccess) {
+    set_error(std::string("residue tables: ") + hipGetErrorString(err));
+    return AWE_ERR_HIP;
   }
   // A wave takes all moduli of its brick, or with few bricks a part of them (which reads the entries
   // once per part), up to 12288 waves: three times the 4 a SIMD holds, so that one wave's loads
@@ -538,7 +604,7 @@ awe_status launch_residue_encode(const ResidueEncodeArgs& e, const ResidueParams
   hipLaunchKernelGGL(residue_encode_kernel,
                      dim3((unsigned)(blocks[0] + blocks[1]), (unsigned)((P.n + g.per_group - 1) / g.per_group)),
                      dim3(256), 0, stream, g);
-  hipError_t err = hipGetLastError();
+  err = hipGetLastError();
   if (err != hipSuccess) {
     set_error(std::string("residue encode launch: ") + hipGetErrorString(err));
     return AWE_ERR_HIP;

@@ -3,6 +3,7 @@ residues of int64 matrices, the Chinese-remainder reconstruction (128-bit words 
 nearest double), and the exact product of 53-bit integer matrices through the FP64
 residue set (23 moduli) at K = 16,384."""
 import os
+import threading
 
 import numpy as np
 import pytest
@@ -272,3 +273,104 @@ def test_residue_planes_at_the_extremes(m):
     want = np.array([[int(v) % m for v in r] for r in x])
     want = np.where(want > m // 2, want - m, want)
     assert np.array_equal(got, want) and flag.item() != 0
+
+
+def _crt_call(ms, M, N, K, seed):
+    """Operands, a call of gemm_crt on buffers of its own (call(stream)), and a check of its result."""
+    bound = 1000
+    rng = np.random.default_rng(seed)
+    A = rng.integers(-bound, bound, size=(M, K), dtype=np.int64, endpoint=True)
+    B = rng.integers(-bound, bound, size=(K, N), dtype=np.int64, endpoint=True)
+    dA, dB = to_dev(A), to_dev(B)
+    ws = torch.empty(awe.crt_workspace_bytes(ms, M, N, K), dtype=torch.uint8, device="cuda")
+    c128 = torch.zeros((M, N, 2), dtype=torch.int64, device="cuda")
+    c64 = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+
+    def call(stream=None):
+        awe.gemm_crt(M, N, K, dA, K, dB, N, bound, bound, ms, c128, c64, N, ws, ws.numel(), None, stream)
+
+    def check(A=A, B=B):
+        ref = og.gemm_i128(A, B)
+        assert (_words_to_ints(c128) == ref).all()
+        assert np.array_equal(c64.cpu().numpy(), ocrt.to_double(ref))
+
+    return dA, dB, call, check
+
+
+@pytest.mark.parametrize("shape", [(33, 40, 300), (520, 300, 1000)])
+def test_gemm_crt_graph_capture_replays(shape):
+    # captured after an eager call with the same moduli: every replay, on new operands in the same memory
+    # and with eager work and synchronisations in between, gives the exact product
+    M, N, K = shape
+    dA, dB, call, check = _crt_call(_moduli()[:9], M, N, K, 3)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        call()
+    torch.cuda.synchronize()
+    check()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        call()
+    rng = np.random.default_rng(8)
+    for rep in range(3):
+        A = rng.integers(-1000, 1000, size=(M, K), dtype=np.int64, endpoint=True)
+        B = rng.integers(-1000, 1000, size=(K, N), dtype=np.int64, endpoint=True)
+        dA.copy_(torch.from_numpy(A))
+        dB.copy_(torch.from_numpy(B))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        check(A, B)
+
+
+def test_gemm_crt_new_moduli_beside_a_capture():
+    # the first call with some moduli, on its own stream, while another thread has a capture of the global
+    # kind open: neither disturbs the other.  (The moduli of this test and the next are in no other.)
+    warm = _crt_call([53, 59, 61, 67, 71], 33, 40, 300, 1)  # sets the kernels' LDS limits
+    warm[2]()
+    _, _, call, check = _crt_call([101, 103, 107, 109, 113], 33, 40, 300, 2)
+    own, failed = torch.cuda.Stream(), []
+
+    def first_call():
+        try:
+            call(own.cuda_stream)
+        except awe.AweError as e:
+            failed.append(e)
+
+    x = torch.zeros(1000, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="global"):
+        x.add_(1)
+        t = threading.Thread(target=first_call)
+        t.start()
+        t.join()
+        x.add_(2)
+    assert not failed, failed
+    torch.cuda.synchronize()
+    check()
+    for rep in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert bool((x == 3 * (rep + 1)).all())
+
+
+def test_gemm_crt_new_moduli_wait_for_no_other_stream():
+    # the first call with some moduli returns while the null stream is busy, on a stream that does not
+    # wait for it; a call on a second stream straight after it uses the same tables
+    warm = _crt_call([53, 59, 61, 67, 71], 33, 40, 300, 1)
+    warm[2]()
+    ms = [127, 131, 137, 143, 145]
+    first, second = _crt_call(ms, 33, 40, 300, 5), _crt_call(ms, 33, 40, 300, 6)
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    busy = torch.cuda.Event()
+    torch.cuda._sleep(100_000_000)  # 50 ms at 2 GHz
+    busy.record()
+    first[2](s1.cuda_stream)
+    second[2](s2.cuda_stream)
+    returned_early = not busy.query()
+    torch.cuda.synchronize()
+    assert returned_early
+    first[3]()
+    second[3]()
