@@ -121,8 +121,9 @@ inline unsigned encode_args(const EncodeLaunch& e, EncodeArgs& a) {
   a.KS = (e.K + kKPad - 1) / kKPad * kKPad / kBrickK;
   a.R32 = rb;
   // one brick per wave (the B side in groups of four column blocks, the last group padded); past
-  // 2^23 workgroups the waves walk several bricks each.  A wide encoding's workgroups stage 16 KiB
-  // of table each: past 2048 of them (8 per CU) their waves walk several bricks.
+  // 2^22 workgroups the waves walk several bricks each (both sides' workgroups go into one launch,
+  // which takes fewer than 2^32 threads).  A wide encoding's workgroups stage 16 KiB of table
+  // each: past 2048 of them (8 per CU) their waves walk several bricks.
   a.nbricks = e.transposed ? (rb + 3) / 4 * 4 * a.KS : rb * a.KS;
   a.nplanes = e.nplanes;
   a.nplanes8 = e.nplanes8;
@@ -130,7 +131,7 @@ inline unsigned encode_args(const EncodeLaunch& e, EncodeArgs& a) {
   a.planes = e.planes;
   a.plane_stride = e.plane_stride;
   a.flag = e.flag;
-  return (unsigned)std::min<int64_t>((a.nbricks + 3) / 4, e.wide ? 2048 : (int64_t(1) << 23));
+  return (unsigned)std::min<int64_t>((a.nbricks + 3) / 4, e.wide ? 2048 : (int64_t(1) << 22));
 }
 
 }  // namespace
