@@ -638,6 +638,19 @@ constexpr VariantCost kVariants[] = {
     {32, 32, 3.0, {0.29, 0.38}},   {32, 64, 4.3, {0.385, 0.50}}, {64, 32, 4.3, {0.375, 0.48}},
 };
 
+// A variant's tiles for an M x N output, or 0 for more than 64 rounds of them: past that it is no longer
+// the better choice, and its kernel counts tiles and the bytes of row blocks in 32 bits.
+int64_t variant_tiles(int variant, int64_t M, int64_t N, int cus) {
+  const VariantCost& c = kVariants[variant - 1];
+  const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+  return tiles <= 64 * (int64_t)cus ? tiles : 0;
+}
+// AWE_GEMM_SLICE's variant for a launch, where the kernel takes it: 1 .. 6, else 0.
+int forced_variant(const char* e, const GemmLaunch& L, int cus) {
+  const int v = atoi(e);
+  return v >= 1 && v <= 6 && variant_tiles(v, L.M, L.N, cus) ? v : 0;
+}
+
 // Whether the environment asks for particular tile configurations or splits.
 bool tuning_overrides() {
   for (const char* name : {"AWE_GEMM_CFG", "AWE_GEMM_CFG_E2M3", "AWE_GEMM_CFG_SHARED", "AWE_GEMM_ALLPAIRS",
@@ -653,10 +666,9 @@ Slice choose_slice(const GemmLaunch& L, int cus, double tile_us) {
   // AWE_GEMM_SLICE: 0 none, 1 .. 6 that variant (AWE_GEMM_SLICE_SPLIT workgroups per tile); the
   // overrides of the tile configurations leave none.  They change no result.
   if (const char* e = tuning("AWE_GEMM_SLICE")) {
-    const int v = atoi(e);
     const char* sp = tuning("AWE_GEMM_SLICE_SPLIT");
     const int split = sp && !L.modulus ? atoi(sp) : 1;
-    return Slice{v >= 1 && v <= 6 ? v : 0, split >= 1 && split <= 64 ? split : 1};
+    return Slice{forced_variant(e, L, cus), split >= 1 && split <= 64 ? split : 1};
   }
   if (tuning_overrides()) return Slice{0, 1};
   const int64_t len = L.k_end - L.k_begin;
@@ -665,8 +677,8 @@ Slice choose_slice(const GemmLaunch& L, int cus, double tile_us) {
   double best_us = tile_us;
   for (int v = 0; v < 6; ++v) {
     const VariantCost& c = kVariants[v];
-    const int64_t tiles = ((L.M + c.bm - 1) / c.bm) * ((L.N + c.bn - 1) / c.bn);
-    if (tiles > 64 * cus) continue;
+    const int64_t tiles = variant_tiles(v + 1, L.M, L.N, cus);
+    if (!tiles) continue;
     const double ns = c.per_index[L.fmt == kFmtE2M3 ? 1 : 0];
     const double us = 4.0 + (double)((tiles + cus - 1) / cus) * (c.fixed + ns * 1e-3 * rk);
     if (us < best_us) {
@@ -687,13 +699,13 @@ Slice choose_slice(const GemmLaunch& L, int cus, double tile_us) {
 }
 
 int choose_slice_group(const GemmLaunch* L, int n, int cus, double tile_us) {
-  if (const char* e = tuning("AWE_GEMM_SLICE")) return atoi(e) >= 1 && atoi(e) <= 6 ? atoi(e) : 0;
+  if (const char* e = tuning("AWE_GEMM_SLICE")) return forced_variant(e, L[0], cus);
   if (tuning("AWE_GEMM_CFG")) return 0;
   int best = 0;
   for (int v = 0; v < 6; ++v) {
     const VariantCost& c = kVariants[v];
-    const int64_t tiles = ((L[0].M + c.bm - 1) / c.bm) * ((L[0].N + c.bn - 1) / c.bn);
-    if (tiles > 64 * cus) continue;
+    const int64_t tiles = variant_tiles(v + 1, L[0].M, L[0].N, cus);
+    if (!tiles) continue;
     double sum = 0.0, longest = 0.0;
     for (int j = 0; j < n; ++j) {
       const double t = c.fixed + c.per_index[0] * 1e-3 * (double)L[j].r * (double)(L[j].k_end - L[j].k_begin);

@@ -1,9 +1,16 @@
 // Host-side checks of the encoder's and the small-output kernels' launch shapes (no GPU needed).
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <initializer_list>
 
-#include "encode_device.h"
+#include "awe_small.hip"
+
+// (what the launchers of this translation unit call; they are not run here)
+namespace awe {
+void set_error(const std::string&) {}
+awe_status set_lds_limit(const void*, int, std::mutex&, std::set<int>&) { return AWE_ERR_HIP; }
+}  // namespace awe
 
 using namespace awe;
 
@@ -36,8 +43,45 @@ static void encoder_grids() {
         }
 }
 
+// The kernel whose waves split the reduction counts tiles and the bytes of a side's row blocks in 32
+// bits: whatever chooses it, a variant is only taken where they fit.
+static void slice_tiles() {
+  const int cus = 256;
+  for (const char* forced : {"", "1", "2", "3", "4", "5", "6"}) {
+    if (*forced)
+      setenv("AWE_GEMM_SLICE", forced, 1);
+    else
+      unsetenv("AWE_GEMM_SLICE");
+    read_tuning();
+    int taken = 0;
+    for (int64_t M : {1ll, 300ll, 8192ll, 1ll << 20, 1ll << 24, 1ll << 27, 0x7fffff00ll})
+      for (int64_t N : {1ll, 300ll, 8192ll, 1ll << 20, 1ll << 24, 0x7fffff00ll}) {
+        GemmLaunch L{};
+        L.M = M;
+        L.N = N;
+        L.K = 512;
+        L.k_end = 512;
+        L.r = L.flat.r = 6;
+        L.flat.k_seg = 512;
+        L.modulus = 89;
+        const Slice s = choose_slice(L, cus, 1e30);
+        const int group = choose_slice_group(&L, 1, cus, 1e30);
+        for (int v : {s.variant, group}) {
+          if (v == 0) continue;
+          ++taken;
+          const VariantCost& c = kVariants[v - 1];
+          const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * s.split;
+          check(tiles * kMaxModuli <= 0x7fffffff, "tiles", M, N);
+          check(((M > N ? M : N) + 31) / 32 * 3 * kBrickBytes < (int64_t)1 << 32, "row blocks", M, N);
+        }
+      }
+    check(taken >= 8, "variants taken where they fit", atoi(forced), taken);
+  }
+}
+
 int main() {
   encoder_grids();
+  slice_tiles();
   std::printf("failures %d\n", fails);
   return fails ? 1 : 0;
 }
