@@ -442,7 +442,6 @@ awe_status rns_setup(const int32_t* moduli, int32_t n, ResidueParams* rp, CrtPar
 }
 
 struct CrtLayout {  // workspace of awe_gemm_crt
-  size_t luts;                   // the moduli's code tables, A side then B side (n x 1 KiB each)
   size_t planes_a, planes_b;     // every modulus's stored planes of A, then of B
   int64_t off_a[kMaxModuli], off_b[kMaxModuli];
   size_t res_c;                  // the n residue products, one byte each (m <= 256)
@@ -452,7 +451,6 @@ struct CrtLayout {  // workspace of awe_gemm_crt
 CrtLayout crt_layout(const int32_t* moduli, int32_t n, int64_t M, int64_t N, int64_t K, awe_status* st) {
   CrtLayout L{};
   *st = AWE_OK;
-  L.luts = (size_t)round_up(2 * (int64_t)n * 256 * 4, 256);
   int64_t pa = 0, pb = 0;
   for (int j = 0; j < n; ++j) {
     const Scheme* s = scheme_or_fail(AWE_ENC_MOD, moduli[j], st);
@@ -465,7 +463,7 @@ CrtLayout crt_layout(const int32_t* moduli, int32_t n, int64_t M, int64_t N, int
   L.planes_a = (size_t)round_up(pa, 256);
   L.planes_b = (size_t)round_up(pb, 256);
   L.res_c = (size_t)round_up((int64_t)n * M * N, 256);
-  L.total = L.luts + L.planes_a + L.planes_b + L.res_c;
+  L.total = L.planes_a + L.planes_b + L.res_c;
   return L;
 }
 
@@ -696,8 +694,7 @@ awe_status awe_gemm_crt(int64_t M, int64_t N, int64_t K, const int64_t* A, int64
   if (st != AWE_OK) return st;
   if (L.total > 0 && (workspace == nullptr || ws_bytes < L.total))
     return fail(AWE_ERR_WORKSPACE, "workspace smaller than awe_crt_workspace_bytes");
-  uint8_t* ws = reinterpret_cast<uint8_t*>(workspace);
-  uint8_t* pla = ws + L.luts;
+  uint8_t* pla = reinterpret_cast<uint8_t*>(workspace);
   uint8_t* plb = pla + L.planes_a;
   uint8_t* rc = plb + L.planes_b;
   if (K > 0) {
@@ -726,8 +723,7 @@ awe_status awe_gemm_crt(int64_t M, int64_t N, int64_t K, const int64_t* A, int64
       }
       r.flag = d_range_flag;
     }
-    e[0].other = &e[1];
-    st = launch_residue_encode(e[0], rp, false, stream);
+    st = launch_residue_encode(e, rp, stream);
     if (st != AWE_OK) return st;
   }
   // the n mod-m GEMMs: one grouped launch when each is a single launch (AWE_GEMM_GROUPED=0

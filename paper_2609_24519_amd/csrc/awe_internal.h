@@ -275,10 +275,9 @@ struct ResidueEncodeArgs {
   int64_t off[kMaxModuli];
   int32_t np[kMaxModuli];
   int32_t* flag;
-  const ResidueEncodeArgs* other;  // the other operand of the product, in the same launch (nullable)
 };
-awe_status launch_residue_encode(const ResidueEncodeArgs& a, const ResidueParams& P, bool transposed,
-                                 hipStream_t stream);
+// Both operands of a product, A then B, in one launch.
+awe_status launch_residue_encode(const ResidueEncodeArgs (&sides)[2], const ResidueParams& P, hipStream_t stream);
 
 struct CrtModulus {
   uint32_t m;

@@ -484,11 +484,10 @@ struct ModTables {
   bool pending = false;  // `done` has not been seen complete
 };
 
-// Makes the tables of both operands' moduli (sides[0] A's, sides[1] B's, nullable) readable by what
-// `stream` is given next, each written once per device (a table depends on its modulus alone).  The
+// Makes the tables of both operands' moduli readable by what `stream` is given next, each written once per device (a table depends on its modulus alone).  The
 // host does not wait, unless `stream` is being captured before tables it needs are seen complete: a
 // captured wait could not refer to them.
-hipError_t ensure_mod_tables(const ResidueEncodeArgs* const (&sides)[2], const uint32_t* m, int n, hipStream_t stream) {
+hipError_t ensure_mod_tables(const ResidueEncodeArgs (&sides)[2], const uint32_t* m, int n, hipStream_t stream) {
   static std::mutex mu;
   static std::map<int, ModTables> devices;
   int dev = 0;
@@ -498,7 +497,7 @@ hipError_t ensure_mod_tables(const ResidueEncodeArgs* const (&sides)[2], const u
   ModTables& t = devices[dev];
   int missing[2 * kMaxModuli], count = 0;  // side n + j
   for (int s = 0; s < 2; ++s)
-    for (int j = 0; sides[s] && j < n; ++j)
+    for (int j = 0; j < n; ++j)
       if (!t.have[s * 255 + m[j] - 2]) missing[count++] = s * n + j;
   if (count == 0 && !t.pending) return hipSuccess;
 
@@ -513,7 +512,7 @@ hipError_t ensure_mod_tables(const ResidueEncodeArgs* const (&sides)[2], const u
         const int s = missing[i + b] / n, j = missing[i + b] % n;
         a.side[b] = (uint16_t)s;
         a.m[b] = (uint16_t)m[j];
-        for (uint32_t r = 0; r < m[j]; ++r) a.code[b][r] = (uint16_t)(sides[s]->luts[j][r] & 0xfffu);
+        for (uint32_t r = 0; r < m[j]; ++r) a.code[b][r] = (uint16_t)(sides[s].luts[j][r] & 0xfffu);
       }
       hipLaunchKernelGGL(mod_table_kernel, dim3((unsigned)k), dim3(256), 0, t.stream, a);
       err = hipGetLastError();
@@ -538,9 +537,7 @@ hipError_t ensure_mod_tables(const ResidueEncodeArgs* const (&sides)[2], const u
 }
 }  // namespace
 
-awe_status launch_residue_encode(const ResidueEncodeArgs& e, const ResidueParams& P, bool transposed,
-                                 hipStream_t stream) {
-  const ResidueEncodeArgs* sides[2] = {transposed ? e.other : &e, transposed ? &e : e.other};
+awe_status launch_residue_encode(const ResidueEncodeArgs (&sides)[2], const ResidueParams& P, hipStream_t stream) {
   ResidueArgs g{};
   int64_t blocks[2] = {0, 0}, bricks = 0;
   for (int j = 0; j < P.n; ++j) {
@@ -558,8 +555,7 @@ awe_status launch_residue_encode(const ResidueEncodeArgs& e, const ResidueParams
     k.init = (m - pw[7] * 128 % m) % m;
   }
   for (int s = 0; s < 2; ++s) {
-    if (!sides[s] || sides[s]->nbricks == 0) continue;
-    const ResidueEncodeArgs& a = *sides[s];
+    const ResidueEncodeArgs& a = sides[s];
     ResidueSide& o = g.side[s];
     o.x = a.x;
     o.rows = a.rows;

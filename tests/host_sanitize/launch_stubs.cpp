@@ -21,7 +21,7 @@ awe_status launch_residues(const int64_t*, int64_t, int64_t, int64_t, int64_t, c
   ++g_launches;
   return AWE_OK;
 }
-awe_status launch_residue_encode(const ResidueEncodeArgs&, const ResidueParams&, bool, hipStream_t) {
+awe_status launch_residue_encode(const ResidueEncodeArgs (&)[2], const ResidueParams&, hipStream_t) {
   ++g_launches;
   return AWE_OK;
 }

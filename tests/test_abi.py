@@ -128,6 +128,13 @@ def test_plane_bytes():
 def test_residue_number_system_host_checks():
     fp64 = [5, 7, 8, 9, 11, 13, 31, 37, 41, 43, 47, 53, 59, 61, 67, 71, 73, 79, 83, 89, 149, 151, 157]
     assert awe.crt_workspace_bytes(fp64, 4096, 4096, 16384) > 23 * 4096 * 4096 * 6
+    # its planes of both operands and its byte residues, no more
+    def padded(b):
+        return -(-b // 256) * 256
+    for ms, M, N, K in ((fp64, 300, 200, 1000), ([7], 1, 1, 1), (fp64[:3], 33, 70, 0)):
+        planes = [padded(sum(awe.plane_bytes(awe.ENC_MOD, m, side, rows, K) for m in ms))
+                  for side, rows in ((awe.SIDE_A, M), (awe.SIDE_B, N))]
+        assert awe.crt_workspace_bytes(ms, M, N, K) == sum(planes) + padded(len(ms) * M * N)
     for bad in ([4, 6], [1, 3], [300], [], list(range(2, 40))):
         with pytest.raises(awe.AweError) as e:
             awe.crt_workspace_bytes(bad, 4, 4, 4)
