@@ -687,6 +687,7 @@ Slice choose_slice(const GemmLaunch& L, int cus, double tile_us) {
     }
     // S workgroups per tile while they fill one round: C zeroed first, S atomic additions per output
     // (270 per ns in all); at least two items per workgroup and product
+    // on average, the padding counted (the last workgroups may have fewer or none)
     for (int s = 2; !L.modulus && s <= 64 && tiles * s <= cus && len >= 256 * s; s *= 2) {
       const double t = 8.0 + c.fixed + ns * 1e-3 * rk / s + s * outs / 270e3;
       if (t < best_us) {

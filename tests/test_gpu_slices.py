@@ -94,6 +94,17 @@ def test_split_of_every_tile(monkeypatch, parts, enc, out):
     assert np.array_equal(_product(enc, A, B, out, ldc_pad=1), oracle_gemm.gemm_i64(A, B))
 
 
+@pytest.mark.parametrize("K,parts", [(1, "2"), (257, "3"), (257, "4"), (1025, "5"), (1100, "4")])
+def test_short_and_empty_parts(monkeypatch, K, parts):
+    # stages of 128: one, 3 (one each; more parts than stages), 9 in 5 parts (the last has one), 9 in 4
+    # (3, 3, 3 and none)
+    monkeypatch.setenv("AWE_GEMM_CFG", "17")
+    monkeypatch.setenv("AWE_GEMM_SPLIT", parts)
+    for out in (torch.int32, torch.int64):
+        A, B = _operands(awe.ENC_AWE6, 300, 270, K, int(parts))
+        assert np.array_equal(_product(awe.ENC_AWE6, A, B, out, ldc_pad=1), oracle_gemm.gemm_i64(A, B))
+
+
 def test_chosen_route_on_mixed_shapes():
     # the library's own choice, over shapes that take different routes
     for enc, M, N, K in [(awe.ENC_AWE6, 16, 2000, 1500), (awe.ENC_B13, 700, 130, 900), (awe.ENC_AWE6, 64, 64, 20000),
