@@ -14,9 +14,8 @@ WRITE_SIZE, each in KiB per dispatch) of a command that also ran a plain
 device copy of a known size (``bench.py --calibrate-copy``), scales every
 kernel's counters by what the counters read for that copy, and records the
 per-dispatch HBM bytes of the GEMM together with a hash of the kernel sources
-they were taken on (the kernels, the GEMM's addressing header and the encoders'
-plane packing), so that a
-later change to either makes them stale.
+they were taken on (KERNEL_SOURCES), so that a later change to any of them makes them
+stale.
 ``counters`` summarises one or more ``--pmc`` passes over the same command:
 per kernel the FP4 MFMA operation count (checked against the algorithmic
 r 2MNK), MFMA busy cycles, LDS bank conflicts and activity, L2 hit rate and
@@ -30,10 +29,11 @@ import os
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-# the GEMM's and the encoder's kernel code, their shared device helpers and the GEMM's addressing (tile
+# the GEMM's and the encoder's kernel code, the kernels for outputs of few tiles and their choice (which
+# decides whether the GEMM runs at all), the shared device helpers and the GEMM's addressing (tile
 # configurations, copy / LDS / fragment offsets)
-KERNEL_SOURCES = tuple(os.path.join(HERE, "csrc", f) for f in ("awe_kernels.hip", "gemm_layout.h", "gemm_device.h",
-                                                               "encode_device.h", "plane_pack.h"))
+KERNEL_SOURCES = tuple(os.path.join(HERE, "csrc", f) for f in ("awe_kernels.hip", "awe_small.hip", "gemm_layout.h",
+                                                               "gemm_device.h", "encode_device.h", "plane_pack.h"))
 COPY_BYTES = 1 << 30  # bench.py --calibrate-copy copies 1 GiB
 
 
@@ -46,8 +46,7 @@ def kernel_source_hash():
 
 
 _LABELS = (  # first match wins
-    ("residue_encode_kernel<true>", "residue_encode_kernel (B side, transposed)"),
-    ("residue_encode_kernel<false>", "residue_encode_kernel (A side)"),
+    ("mod_table_kernel", "mod_table_kernel (code tables, once per modulus)"),
     ("residue_encode_kernel", "residue_encode_kernel (both operands)"),
     ("residues_kernel", "residues_kernel"),
     ("crt_kernel", "crt_kernel"),
@@ -62,6 +61,7 @@ _LABELS = (  # first match wins
     ("encode_kernel<false>", "encode_kernel (A side)"),
     ("zero_tiles_kernel", "zero_tiles_kernel"),
     ("fill_zero_kernel", "fill_zero_kernel"),
+    ("zero_kernel", "zero_kernel"),
     ("distribution_elementwise", "input generation (torch random)"),
 )
 

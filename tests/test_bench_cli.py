@@ -53,6 +53,35 @@ def test_kernel_source_hash_tracks_the_kernel_file():
     assert h == profiling.kernel_source_hash() and len(h) >= 8
 
 
+def test_kernel_source_hash_covers_what_the_byte_products_include(tmp_path, monkeypatch):
+    # the sources of the two translation units whose kernels the byte products run, and every device
+    # header either includes; a change in any one changes the hash
+    from paper_2609_24519_amd import profiling
+
+    csrc = os.path.join(ROOT, "paper_2609_24519_amd", "csrc")
+    files, todo = set(), ["awe_kernels.hip", "awe_small.hip"]
+    while todo:
+        f = todo.pop()
+        if f in files or f == "awe_internal.h":  # (host-side declarations)
+            continue
+        files.add(f)
+        with open(os.path.join(csrc, f)) as src:
+            todo += [l.split('"')[1] for l in src if l.startswith('#include "')]
+    assert {os.path.basename(p) for p in profiling.KERNEL_SOURCES} == files
+    copies = []
+    for p in profiling.KERNEL_SOURCES:
+        copies.append(str(tmp_path / os.path.basename(p)))
+        with open(p) as src, open(copies[-1], "w") as dst:
+            dst.write(src.read())
+    monkeypatch.setattr(profiling, "KERNEL_SOURCES", tuple(copies))
+    seen = {profiling.kernel_source_hash()}
+    for p in copies:
+        with open(p, "a") as f:
+            f.write("\n")
+        seen.add(profiling.kernel_source_hash())
+    assert len(seen) == len(copies) + 1
+
+
 def test_clock_table_from_bench_line(tmp_path):
     import json
 
@@ -79,8 +108,11 @@ def test_kernel_labels():
     from paper_2609_24519_amd import profiling
 
     ns = "void awe::(anonymous namespace)::"
-    assert profiling._short(ns + "residue_encode_kernel<true>(awe::ResidueEncodeArgs)") == \
-        "residue_encode_kernel (B side, transposed)"
+    assert profiling._short(ns + "residue_encode_kernel(awe::ResidueArgs)") == \
+        "residue_encode_kernel (both operands)"
+    assert profiling._short(ns + "encode_pair_kernel(awe::EncodeArgs)") == "encode_pair_kernel (both operands)"
+    assert profiling._short(ns + "fill_zero_kernel(unsigned char*)") == "fill_zero_kernel"
+    assert profiling._short(ns + "zero_kernel(unsigned int*)") == "zero_kernel"
     assert profiling._short(ns + "encode_kernel<true>(unsigned char const*)") == "encode_kernel (B side, transposed)"
     assert profiling._short(ns + "encode_kernel<false>(unsigned char const*)") == "encode_kernel (A side)"
     assert profiling._short(ns + "gemm_group_kernel<Cfg<4> >(GroupArgs)") == "gemm_group_kernel"
