@@ -1,7 +1,7 @@
 """GPU parity of the exact product against the oracle's plain int64 GEMM (bit-exact).
 
-Small and ragged shapes that span several 256 x 128 tiles and a ragged tail,
-every encoding, both output types, forced small fold segments, reduction
+Small and ragged shapes by the routes the library takes for them, every tile
+configuration (forced) over several tiles and a ragged tail, every encoding, both output types, forced small fold segments, reduction
 lengths that need several launches, the FP32 partial near its 2^23 bound,
 and the degenerate sizes.
 """
@@ -29,6 +29,16 @@ def _run_exact(enc, A, B, out=torch.int32):
 def _operands(enc, M, N, K, seed):
     a_range = {awe.ENC_AWE4: (-8, 7), awe.ENC_TERNARY: (-1, 1)}.get(enc, (-128, 127))
     return inputs.int8_pair(M, N, K, seed, a_range=a_range)
+
+
+# Outputs of fewer tiles than CUs: every tile's reduction in one workgroup ("1"), or split as the library
+# would (None).
+PARTS = pytest.mark.parametrize("parts", ["1", None], ids=["whole", "split"])
+
+
+def _split(monkeypatch, parts):
+    if parts is not None:
+        monkeypatch.setenv("AWE_GEMM_SPLIT", parts)
 
 
 def test_config1_256_cubed():
@@ -176,10 +186,26 @@ def test_multi_launch_reduction():
         assert np.array_equal(C, ref), enc
 
 
-def test_fp32_partial_near_bound_fp6k3():
+def _one_workgroup_per_tile(monkeypatch, route, cfg_name):
+    """Each tile's whole reduction in one workgroup, so that a partial can cover a whole fold segment: tile
+    configuration `route` of cfg_name ("cfg 5"), or a variant of the kernel whose waves split the
+    reduction ("slice 1": two shares of the products one after another, "slice 4": eight)."""
+    kind, n = route.split()
+    if kind == "cfg":
+        monkeypatch.setenv(cfg_name, n)
+        monkeypatch.setenv("AWE_GEMM_SPLIT", "1")
+    else:
+        monkeypatch.setenv("AWE_GEMM_SLICE", n)
+        monkeypatch.setenv("AWE_GEMM_SLICE_SPLIT", "1")
+
+
+@pytest.mark.parametrize("route", ["cfg 3", "cfg 5", "slice 1"])
+def test_fp32_partial_near_bound_fp6k3(monkeypatch, route):
     # the 3-product E2M3 scheme: c_A c_B = 15 * 15 (the sum plane of x = -120 is -8 - 7 = -15),
     # default fold segment 37,120, so with A = B = -120 the sum plane's FP32 partial reaches
-    # 225 * 37120 = 8,352,000, just below 2^23, before its fold with coefficient 16
+    # 225 * 37120 = 8,352,000, just below 2^23, before its fold with coefficient 16 (two shares of three
+    # products: the first and the last product whole, the second in halves)
+    _one_workgroup_per_tile(monkeypatch, route, "AWE_GEMM_CFG_E2M3")
     info = awe.get_encoding_info(awe.ENC_FP6K3)
     K = info["k_seg"]
     assert 225 * K < 2 ** 23 <= 225 * (K + awe.K_PAD)
@@ -192,13 +218,37 @@ def test_fp32_partial_near_bound_fp6k3():
     assert np.array_equal(C.astype(np.int64), og.gemm_i64(A, B))
 
 
-def test_fp32_partial_near_bound():
+def test_fp32_partial_near_bound_weights_as_coefficients(monkeypatch):
+    # the weights-in-scales E2M3 scheme product by product: c_A c_B = 8 * 8, so a partial covers up to
+    # (2^23 - 1) / 64 indices, 130,816 by the padding, which is also all that a launch takes; -120 has the
+    # low limb -8 and -128 the high limb -8, so the partials of products (0, 0) and (1, 1) reach
+    # 64 * 130816 = 8,372,224 (two shares: two whole products each)
+    _one_workgroup_per_tile(monkeypatch, "slice 1", "")
+    K = 130816
+    assert K % awe.K_PAD == 0 and 64 * K < 2 ** 23 <= 64 * (K + awe.K_PAD)
+    lo, T = awe.get_plane_table(awe.ENC_FP6P4, 0, awe.SIDE_A)
+    assert np.abs(T).max() == 8 and list(T[-120 - lo]) == [-8, -7] and list(T[-128 - lo]) == [0, -8]
+    A = np.full((32, K), -120, np.int8)
+    A[1::2] = -128
+    B = np.full((K, 48), -120, np.int8)
+    B[:, 1::3] = -128
+    B[:, 2::3] = 127
+    C = _run_exact(awe.ENC_FP6P4, A, B, torch.int32)
+    assert np.array_equal(C.astype(np.int64), og.gemm_i64(A, B))
+
+
+@pytest.mark.parametrize("route,segments", [("cfg 5", 1), ("cfg 17", 1), ("cfg 17", 2), ("slice 1", 1), ("slice 1", 2),
+                                            ("slice 4", 2)])
+def test_fp32_partial_near_bound(monkeypatch, route, segments):
     # AWE4: c_A c_B = 24, default fold segment = the largest multiple of K_PAD not above
     # (2^23 - 1) / 24 (349440), so one FP32 partial reaches 24 * 349440 = 8386560, just below
-    # 2^23; constant operands put every product at its largest magnitude
+    # 2^23; constant operands put every product at its largest magnitude.  Over two segments a product
+    # folds in between, and eight shares of four products are one segment each
+    _one_workgroup_per_tile(monkeypatch, route, "AWE_GEMM_CFG")
     info = awe.get_encoding_info(awe.ENC_AWE4)
     K = info["k_seg"]
     assert K % awe.K_PAD == 0 and 24 * K < 2 ** 23 <= 24 * (K + awe.K_PAD)
+    K *= segments
     loa, TA = awe.get_plane_table(awe.ENC_AWE4, 0, awe.SIDE_A)
     lob, TB = awe.get_plane_table(awe.ENC_AWE4, 0, awe.SIDE_B)
     xs = [x for x in range(loa, loa + TA.shape[0]) if np.abs(TA[x - loa]).max() == 3]
@@ -236,12 +286,14 @@ def test_mod_forced_segments():
 
 @pytest.mark.parametrize("cfg", ["1", "2", "4", "5", "6", "7", "8", "9", "10", "12", "13", "15", "16", "17"])
 @pytest.mark.parametrize("enc", [awe.ENC_AWE6, awe.ENC_AWE4, awe.ENC_B13, awe.ENC_TERNARY])
-def test_every_tile_configuration(monkeypatch, cfg, enc):
+@PARTS
+def test_every_tile_configuration(monkeypatch, cfg, enc, parts):
     # AWE_GEMM_CFG forces one of the GEMM's tile configurations (256x128 on 8 waves with
     # 2 or 4 k-steps per stage, 256x192 on 8 waves in 2 or 5 stages, fragments read one or
     # three k-steps ahead or in place, 32x32x64 or 16x16x128 MFMAs, 256x256 with part of
     # the int32 fold accumulators in LDS, copies issued before or after the first MFMAs of a
     # stage); every one must give the exact product
+    _split(monkeypatch, parts)
     monkeypatch.setenv("AWE_GEMM_CFG", cfg)
     monkeypatch.setenv("AWE_GEMM_ALLPAIRS", "0")  # base-13 on the product-major stream here
     M, N, K = 300, 420, 1100
@@ -258,16 +310,18 @@ def test_every_tile_configuration(monkeypatch, cfg, enc):
 
 @pytest.mark.parametrize("cfg", ["16", "17"])
 @pytest.mark.parametrize("shape,kseg,out", [
-    ((256, 256, 1), 0, torch.int32),        # the whole reduction in 2 stages: copies past its end
-    ((300, 420, 257), 0, torch.int32),      # 4 stages, ragged tiles
-    ((512, 512, 1024), 0, torch.int32),     # whole 256 x 256 tiles (16-byte row epilogue)
+    ((256, 256, 1), 0, torch.int32),        # one stage a product: copies past the reduction's end
+    ((300, 420, 257), 0, torch.int32),      # 3 stages, ragged tiles
+    ((512, 512, 1024), 0, torch.int32),     # whole 256 x 256 tiles (16-byte row epilogue, unless split)
     ((512, 256, 3000), 256, torch.int32),   # a fold every 2 stages, whole tiles
     ((260, 520, 1500), 512, torch.int64),   # int64 C, ragged, a fold every 4 stages
 ])
-def test_long_reduction_schedules_edges(monkeypatch, cfg, shape, kseg, out):
+@PARTS
+def test_long_reduction_schedules_edges(monkeypatch, cfg, shape, kseg, out, parts):
     # configs 16 and 17 (256 x 256, copies between the MFMAs, fragments read during the k-step
     # before, config 17's barrier inside the second k-step; 17 is the default for long
     # reductions): reductions of a few stages, forced fold segments, whole and ragged tiles
+    _split(monkeypatch, parts)
     monkeypatch.setenv("AWE_GEMM_CFG", cfg)
     M, N, K = shape
     enc = awe.ENC_AWE6
@@ -297,12 +351,14 @@ def test_ternary_4096_sampled():
 @pytest.mark.parametrize("shape,out", [((70, 45, 500), torch.int32), ((130, 260, 2000), torch.int64),
                                        ((33, 40, 16384), torch.int64), ((16, 24, 120_000), torch.int64),
                                        ((300, 420, 70_000), torch.int64)])
-def test_fp16_12_products(monkeypatch, allpairs, shape, out):
+@PARTS
+def test_fp16_12_products(monkeypatch, allpairs, shape, out, parts):
     # App. A: 12-bit integers (FP16 significands) in 12 FP4 products, by default one launch per
     # reduction range in which each stage brings planes t and t + 3 of each side for the four
     # products (t, k, l) into one accumulator per outer weight 71^(k+l); with
     # AWE_GEMM_ALLPAIRS=0, one launch per outer weight; the last shapes need several reduction
     # launches (and, the last, several fold segments)
+    _split(monkeypatch, parts)
     monkeypatch.setenv("AWE_GEMM_ALLPAIRS", allpairs)
     M, N, K = shape
     rng = np.random.default_rng(M + N + K)
@@ -356,11 +412,13 @@ def test_split_last_round(monkeypatch, cfg, cus, enc, out):
 
 
 @pytest.mark.parametrize("cfg", ["0", "1", "3", "5", "6"])
-def test_every_e2m3_tile_configuration(monkeypatch, cfg):
+@PARTS
+def test_every_e2m3_tile_configuration(monkeypatch, cfg, parts):
     # AWE_GEMM_CFG_E2M3 forces one of the E2M3 tile configurations (256x128 on 8 waves
     # in 3 or 4 stages, with 4 k-steps per stage; 256x192 on 8 waves with fragments read in
     # place and the int32 fold accumulators of 1 or 2 blocks per wave in LDS); each must be
     # exact, also with a forced fold segment of one K_PAD
+    _split(monkeypatch, parts)
     monkeypatch.setenv("AWE_GEMM_CFG_E2M3", cfg)
     M, N, K = 300, 420, 1100
     A, B = _operands(awe.ENC_FP6K3, M, N, K, seed=int(cfg) + 70)
@@ -390,12 +448,14 @@ def test_fp6k3_8192():
 
 
 @pytest.mark.parametrize("cfg", ["0", "1"])
-def test_shared_accumulator_configurations(monkeypatch, cfg):
+@PARTS
+def test_shared_accumulator_configurations(monkeypatch, cfg, parts):
     # INT8 x INT8 in 4 E2M3 products with the weights in the block scales: both tile
     # configurations (fragments read ahead or in place), the default fold segment and a
     # forced one of one K_PAD, and the accumulator near its bound: x = y = 120 makes every
     # reduction index add 18,496 in absolute terms, and the default segment (768 indices)
-    # brings the FP32 accumulator to 14,400 * 768 = 11,059,200 of 2^24
+    # brings the FP32 accumulator to 14,400 * 768 = 11,059,200 of 2^24 (where no tile is split)
+    _split(monkeypatch, parts)
     monkeypatch.setenv("AWE_GEMM_CFG_SHARED", cfg)
     M, N, K = 300, 420, 1100
     A, B = _operands(awe.ENC_FP6P4, M, N, K, seed=int(cfg) + 90)
@@ -429,10 +489,12 @@ def test_fp6p4_8192():
 @pytest.mark.parametrize("shape,out,kseg", [((1, 1, 1), torch.int32, 0), ((300, 420, 1100), torch.int32, 0),
                                             ((129, 513, 3000), torch.int64, 256),
                                             ((700, 300, 2100), torch.int64, 512)])
-def test_base13_all_pairs_stream(monkeypatch, allpairs, shape, out, kseg):
+@PARTS
+def test_base13_all_pairs_stream(monkeypatch, allpairs, shape, out, kseg, parts):
     # base-13's nine limb pairs with one accumulator per coefficient 13^(i + j): each stage
     # brings the three planes of each side once (default), or the product-major stream
     # (AWE_GEMM_ALLPAIRS=0); ragged shapes, both outputs, forced fold segments
+    _split(monkeypatch, parts)
     monkeypatch.setenv("AWE_GEMM_ALLPAIRS", allpairs)
     M, N, K = shape
     enc = awe.ENC_B13

@@ -144,7 +144,7 @@ def test_gemm_crt_full(shape):
     assert np.array_equal(c64.cpu().numpy(), ocrt.to_double(ref))
 
 
-@pytest.mark.parametrize("grouped,cfg", [("1", None), ("0", None), ("1", "4"), ("1", "1"), ("1", "6"), ("1", "13"),
+@pytest.mark.parametrize("grouped,cfg", [("1", None), ("0", None), ("1", "4"), ("1", "1"), ("1", "5"), ("1", "6"), ("1", "13"),
                                           ("1", "16"), ("1", "17")])
 def test_gemm_crt_grouped_launch(monkeypatch, grouped, cfg):
     # the moduli's GEMMs run as one grouped launch (jobs with the most products first) or,
@@ -213,7 +213,7 @@ def test_gemm_crt_4096_sampled():
 
 def test_gemm_crt_range_flag_and_large_entries():
     # entries beyond the stated bound set the flag (both operands), and entries at or beyond
-    # 2^53 (the integer residue route instead of the double one) still give exact residues;
+    # 2^53 still give exact residues;
     # the product stays within the moduli's range, so C is exact too
     ms = _moduli()
     M, N, K = 33, 40, 300
@@ -224,7 +224,7 @@ def test_gemm_crt_range_flag_and_large_entries():
                                   (1 << 60, 1000, True)):
         Ai = A.copy()
         if big:
-            Ai[3, 7] = (1 << 53) + 5  # a wave of A entries takes the integer route
+            Ai[3, 7] = (1 << 53) + 5
             Ai[4, 9] = -(1 << 60)
         flag = torch.zeros(1, dtype=torch.int32, device="cuda")
         c128, c64 = awe.matmul_crt(to_dev(Ai), to_dev(B), ms, bound_a, bound_b, flag)

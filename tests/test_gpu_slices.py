@@ -86,10 +86,17 @@ def test_several_launches_add_up(monkeypatch):
 @pytest.mark.parametrize("parts", ["2", "3", "5"])
 @pytest.mark.parametrize("enc,out", [(awe.ENC_AWE6, torch.int32), (awe.ENC_AWE4, torch.int64), (awe.ENC_B13, torch.int32),
                                      (awe.ENC_FP6K3, torch.int32), (awe.ENC_FP6P4, torch.int64),
-                                     (awe.ENC_FP8FP4, torch.int32)])
+                                     (awe.ENC_FP8FP4, torch.int32), (awe.ENC_FP16, torch.int64),
+                                     (awe.ENC_FP16, torch.int32)])
 def test_split_of_every_tile(monkeypatch, parts, enc, out):
     # fewer tiles than CUs: each tile's reduction in `parts` parts, the last one shorter
     monkeypatch.setenv("AWE_GEMM_SPLIT", parts)
+    if enc == awe.ENC_FP16:  # (its parts add through the epilogue of the outer groups)
+        rng = np.random.default_rng(int(parts))
+        K = 2900 if out == torch.int64 else 500  # what int32 holds
+        A, B = (inputs.uniform(rng, s, -2048, 2047, np.int16) for s in ((300, K), (K, 270)))
+        assert np.array_equal(_product(enc, A, B, out, ldc_pad=1), oracle_gemm.gemm_i64_wide(A, B))
+        return
     A, B = _operands(enc, 300, 270, 2900, int(parts))
     assert np.array_equal(_product(enc, A, B, out, ldc_pad=1), oracle_gemm.gemm_i64(A, B))
 
