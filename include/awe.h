@@ -212,7 +212,7 @@ awe_status awe_gemm_exact(awe_encoding enc, int64_t M, int64_t N, int64_t K,
    and calls no allocating routine.  Arguments, layouts, results and errors as awe_gemm_exact,
    and AWE_ERR_WORKSPACE when awe_workspace_bytes for these sizes exceeds AWE_NOALLOC_MAX_BYTES
    (nothing is enqueued then).  Every call on a GPU uses that GPU's one array, which keeps the
-   last call's planes (a call reads only planes it has written): calls that overlap on one GPU
+   planes of the last call that stored any (a call reads only planes it has written): calls that overlap on one GPU
    (other streams, other threads) race on it and give wrong results; order them on one stream.
    The first call on a device looks up the array's address (host side), and like awe_gemm_exact
    sets the GEMM's LDS limit and, for AWE_ENC_FP16, uploads its code table: make that first

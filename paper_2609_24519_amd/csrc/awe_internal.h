@@ -235,9 +235,11 @@ awe_status launch_direct(const GemmLaunch& L, hipStream_t stream);
 // choose_slice for launches that share one (launch_gemm_group's; order: the jobs' order).
 int choose_slice_group(const GemmLaunch* L, int n, int cus, double tile_us);
 awe_status launch_slice_group(const GemmLaunch* L, const int* order, int n, int variant, hipStream_t stream);
-// Time of a grouped launch (us): each job has `tiles` tiles, the jobs' tile times add up to `sum`, the
-// longest is `longest`.  Many jobs fill the rounds, so they are not quantised: the CUs' share and a
-// third of a tile for the ragged end, but no less than one tile.
+// Estimated time of a grouped launch (us): each job has `tiles` tiles, the jobs' tile times add up to
+// `sum`, the longest is `longest`.  The CUs' even share and a third of a tile for the ragged end, but
+// no less than one tile; rounds are not counted, so a badly filled last one takes longer (368 tiles of
+// 256 x 256 with 1 to 4 products on 256 CUs, 1024^2 x 4096 and 23 moduli: six product times, where an
+// even share is 3.75).
 inline double group_time(double sum, double longest, int64_t tiles, int cus) {
   const double share = sum * (double)tiles / cus + 0.3 * longest;
   return 4.0 + (share > longest ? share : longest);

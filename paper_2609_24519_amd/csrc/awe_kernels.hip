@@ -896,7 +896,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
     [[maybe_unused]] auto mfma_q = [&](const Frags<C>& cur, auto qc) {
       constexpr int q = decltype(qc)::value, pair = q / (C::BMW * C::BNW), i = q / C::BNW % C::BMW, j = q % C::BNW;
       if constexpr (C::MF == 16)
-        static_assert(C::MF != 16 || q >= 0, "not used for 16x16x128");
+        return;  // (not spread)
       else if constexpr (C::NPL == 2)  // the four plane pairs, each block's MFMAs four apart in issue order
         acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.a[(pair >> 1) * C::BMW + i],
                                                                     cur.b[(pair & 1) * C::BNW + j], acc[i][j], 2, 2, 0,
@@ -1050,7 +1050,7 @@ __device__ __forceinline__ void gemm_tile(GemmArgs g, FoldCoef fold_coef, int ti
   };
   if constexpr (C::MF == 32 && !C::OUTG && C::FMT == 0 && C::NPL == 1) {
     // Whole tiles written (not added): each 32 x 32 block goes through a
-    // per-wave LDS slot (rows of 36 words, 16-byte aligned) so that a elane stores 16 bytes of
+    // per-wave LDS slot (rows of 36 words, 16-byte aligned) so that a lane stores 16 bytes of
     // one row (4 outputs) instead of 16 single outputs of one column: a quarter of the store
     // instructions.  Uniform per workgroup.
     static_assert(C::NW * 32 * 36 * 4 <= C::NSTAGE * C::STAGE_BYTES, "row slots inside the ring");
