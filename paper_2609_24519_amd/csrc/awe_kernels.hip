@@ -1376,8 +1376,9 @@ GroupChoice choose_group_cfg(const GemmLaunch* L, int n) {
 // 8 waves reading fragments in place and the int32 fold accumulators of 1 of each wave's 6
 // blocks in LDS, 6: as 5 with 2 blocks in LDS and 2 stages) if it names one, else 3 or 5, whichever
 // has its rounds done first, a round of 5 taken as 1.4 rounds of 3.  Measured in one process (3 / 5,
-// us): 2048 x 4096 x 4096 69 / 101, 4096^2 x 2048 79 / 115, 4096^3 133 / 176, 5000 x 4000 x 4096 186 /
-// 198, 8192 x 4096 x 4096 265 / 293, 6144^2 x 4096 322 / 299, 8192^3 1115 / 1008; 3000^3 a tie.
+// us, launches of one graph): 2048 x 4096 x 4096 67 / 92, 4096^2 x 2048 79 / 112, 4096^3 133 / 165,
+// 5000 x 4000 x 4096 184 / 187, 8192 x 4096 x 4096 270 / 285, 6144^2 x 4096 315 / 291, 8192^3 1109 /
+// 1012; 3000^3 a tie.
 int choose_cfg_e2m3(const GemmLaunch& L) {
   const char* e = tuning("AWE_GEMM_CFG_E2M3");
   const int forced = e ? atoi(e) : -1;
@@ -1419,8 +1420,10 @@ void fill_args(const GemmLaunch& L, GemmArgs& g) {
 
 // The split of a launch on one tile configuration, with its estimated time: 0.7 time units (10 ns)
 // per 32x32x64 MFMA of a tile (twice that for E4M3's) and 1400 for prologue and epilogue, or 0.5 and
-// 800 where a stage's planes serve several products, near the measured times of every
-// configuration.
+// 800 where a stage's planes serve several products.  Estimated / measured (us): base-13 2048^3 31 /
+// 35, 4096^3 216 / 242, 12-bit significands 39 / 54 and 278 / 364, E2M3 with the weights in the scales
+// 43 / 34 and 143 / 135, E2M3 in 3 products 4096^3 114 / 133: good enough to compare splits of one
+// configuration, and within a third where it is compared with the slices.
 template <class C>
 Split tile_split(const GemmLaunch& L, int cus) {
   const int64_t tiles = ((L.M + C::BM - 1) / C::BM) * ((L.N + C::BN - 1) / C::BN), len = L.k_end - L.k_begin;

@@ -628,7 +628,12 @@ awe_status launch_direct_waves(DirectArgs& d, hipStream_t stream) {
 // The variants' tiles and times on one MI355X: a tile takes about fixed + per_index * r K microseconds
 // (r products, K reduction indices), by format, a round of tiles on all CUs that long, and a launch
 // 4 us more.  Fitted to 2048^3, 1024^3, 512^2 x 8192 and 16 x 8192 x 8192 (E2M1) and 2048^3, 1024^3,
-// 1024^2 x 4096 and 512 x 8192 x 8192 (E2M3).
+// 1024^2 x 4096 and 512 x 8192 x 8192 (E2M3), launched by themselves.  Launches of one graph against
+// the estimate (us, variants 1 to 6): AWE6 2048^3 37, 46, 56, 103, 73, 70 / 36, 49, 57, 109, 76, 75; 1024^3
+// 19, 14, 10, 18, 13, 12 / 25, 20, 13, 23, 17, 17 (all variants about 5 us less, so their order stands);
+// weights in the scales 2048^3 28, 46, 60, 93, 66, 63 / 31, 49, 60, 102, 71, 70.  Over 45 drawn products (E2M1
+// and E2M3, GEMM alone) the choice was within 6 % of the best variant or tile configuration in 42 and 8, 10
+// and 50 % behind it in the others, the last a reduction of 64 indices, which the model takes for 256.
 struct VariantCost {
   int bm, bn;
   double fixed, per_index[2];  // us, ns for E2M1 and E2M3
