@@ -26,9 +26,9 @@
  *    memset, no copy), so they can be captured into a HIP graph once each has been called
  *    eagerly on the device (the first calls set the GEMM's LDS limit and, for the FP16
  *    scheme, upload its code table).  awe_gemm_crt also writes the code tables of its moduli the
- *    first time it meets them on a device, so the same holds for it, modulus by modulus.  It
- *    writes them on a stream of its own, for which `stream` then waits: the host waits for
- *    nothing, and captures that are open elsewhere stay valid.
+ *    first time it meets them on a device, on a stream of its own for which `stream` then waits:
+ *    the host waits for nothing (for the tables, if `stream` is being captured), and captures
+ *    that are open elsewhere stay valid.
  *  - Matrices are row-major: A is M x K (A[i*lda + k]), B is K x N
  *    (B[k*ldb + j]), C is M x N (C[i*ldc + j]).  Leading dimensions must be
  *    at least the row length.  Empty problems (M or N zero) succeed and write

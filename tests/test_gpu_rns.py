@@ -326,7 +326,7 @@ def test_gemm_crt_graph_capture_replays(shape):
 
 def test_gemm_crt_new_moduli_beside_a_capture():
     # the first call with some moduli, on its own stream, while another thread has a capture of the global
-    # kind open: neither disturbs the other.  (The moduli of this test and the next are in no other.)
+    # kind open: neither disturbs the other.  (The moduli of this test and the next two are in no other.)
     warm = _crt_call([53, 59, 61, 67, 71], 33, 40, 300, 1)  # sets the kernels' LDS limits
     warm[2]()
     _, _, call, check = _crt_call([101, 103, 107, 109, 113], 33, 40, 300, 2)
@@ -374,3 +374,18 @@ def test_gemm_crt_new_moduli_wait_for_no_other_stream():
     assert returned_early
     first[3]()
     second[3]()
+
+
+def test_gemm_crt_new_moduli_under_capture():
+    # moduli first met while the caller's own stream is captured: their tables are written outside the graph
+    # and before the call returns, so a replay finds them
+    warm = _crt_call([53, 59, 61, 67, 71], 33, 40, 300, 1)
+    warm[2]()
+    _, _, call, check = _crt_call([121, 125, 129, 133, 128], 33, 40, 300, 9)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for rep in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        check()
