@@ -15,8 +15,9 @@
  *
  * Conventions for every entry point below:
  *  - Pointers are DEVICE pointers unless marked host.  The caller allocates
- *    and owns every buffer; the library keeps only its constant tables (host
- *    memory) and allocates no device memory.
+ *    and owns every buffer; the library keeps only its constant tables (host memory, and
+ *    device arrays that are part of the library) and, once awe_gemm_crt has been called on
+ *    a device, one stream and one event there.  It allocates no device memory.
  *  - Device work is enqueued asynchronously on `stream` (0 = the null
  *    stream).  Argument errors are detected on the host before anything is
  *    enqueued and returned as a status; nothing is written then.  No C++

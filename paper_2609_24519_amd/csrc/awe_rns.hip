@@ -476,7 +476,9 @@ class RelaxedCapture {
 
 // The tables of g_mod_lut on one device.  They are written on a stream of their own, which waits for
 // no other; `done` is recorded behind the latest, and other streams wait for it until it is seen
-// complete.
+// complete.  (On the first caller's stream, every other stream's first call would wait for all that the
+// former still has to do.  Creating the stream is 2.4 of the 5.1 ms that a process's first awe_gemm_crt
+// takes with 23 moduli; later calls return after 22 us either way.)
 struct ModTables {
   std::bitset<2 * 255> have;  // side 255 + m - 2: written, or being written before `done`
   hipStream_t stream = nullptr;
