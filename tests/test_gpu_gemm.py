@@ -308,6 +308,27 @@ def test_every_tile_configuration(monkeypatch, cfg, enc, parts):
 
 
 
+@pytest.mark.parametrize("cfg", ["1", "2", "4", "5", "6", "9", "12", "13", "15", "16", "17"])
+@pytest.mark.parametrize("m", [7, 89, 157])
+def test_residues_of_whole_tiles(monkeypatch, cfg, m):
+    # whole tiles of residues go out four columns at a time where C and ldc allow it: an aligned C, one that
+    # starts one entry later, an odd ldc, and whole and ragged tiles of one output
+    monkeypatch.setenv("AWE_GEMM_CFG", cfg)
+    M, N, K = 512, 772, 300
+    A, B = inputs.residue_pair(M, N, K, m)
+    ref = og.gemm_mod(m, A, B)
+    Ad, Bd = to_dev(A), to_dev(B)
+    n = awe.workspace_bytes(awe.ENC_MOD, m, M, N, K)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    for skip, ldc in ((0, N), (1, N), (0, N + 3), (4, N + 4)):
+        buf = torch.full((skip + M * ldc,), -7, dtype=torch.int32, device="cuda")
+        awe.gemm_mod(m, M, N, K, Ad, K, Bd, N, buf[skip:], ldc, ws, n)
+        got = buf.cpu().numpy()
+        rows = got[skip:].reshape(M, ldc)
+        assert np.array_equal(rows[:, :N], ref), (skip, ldc)
+        assert (got[:skip] == -7).all() and (rows[:, N:] == -7).all(), (skip, ldc)
+
+
 @pytest.mark.parametrize("cfg", ["16", "17"])
 @pytest.mark.parametrize("shape,kseg,out", [
     ((256, 256, 1), 0, torch.int32),        # one stage a product: copies past the reduction's end
